@@ -205,15 +205,20 @@ typedef struct {
  *   depth: list words a wave that reads rows from global memory keeps in
  *     flight (8, 16 or 32);
  *   kernel[c]: the kernel of size class c (c = 0..4 for padded widths
- *     mp = 1024, 512, 256, 128, 64): QB_ANNEAL_AUTO (a replica spread over
- *     up to four waves where its replicas fit one workgroup, else one wave
- *     per replica), QB_ANNEAL_MULTI_WAVE, QB_ANNEAL_ONE_WAVE, or
- *     QB_ANNEAL_ONE_WAVE_REG (one wave per replica holding the current
- *     diagonal block's couplings in registers; tiles in LDS only: int8
- *     mp <= 512, int16 mp <= 128), or QB_ANNEAL_MULTI_WAVE_GLOBAL (a
- *     replica over up to four waves reading the tile rows from global memory,
- *     a few KB of LDS, so that several jobs share a compute unit; R = 1); a
- *     kernel that cannot run the class falls back to the automatic choice;
+ *     mp = 1024, 512, 256, 128, 64): QB_ANNEAL_AUTO (a workgroup per
+ *     replica that decides blocks of positions at once and repairs them,
+ *     unless many jobs have R >= 4 replicas or the class is mp = 1024 with
+ *     int16 tiles or under 8 sweeps: then the next two), QB_ANNEAL_MULTI_WAVE
+ *     (a replica spread over up to four waves where its replicas fit one
+ *     workgroup, else one wave per replica; also the automatic choice while
+ *     qb_set_anneal_wait_limit differs from its default),
+ *     QB_ANNEAL_ONE_WAVE, or QB_ANNEAL_ONE_WAVE_REG (one wave per replica
+ *     holding the current diagonal block's couplings in registers; tiles in
+ *     LDS only: int8 mp <= 512, int16 mp <= 128), or
+ *     QB_ANNEAL_MULTI_WAVE_GLOBAL (a replica over up to four waves reading
+ *     the tile rows from global memory: int8 mp = 1024, int16 mp = 512,
+ *     R = 1); a kernel that cannot run the class falls back to the automatic
+ *     choice;
  *   persistent: 1 = each class runs as a persistent grid of
  *     wgs_per_cu workgroups per compute unit (at most one per job) that pull
  *     the class's jobs from an atomic queue; 0 = one workgroup per job;
@@ -295,7 +300,8 @@ qb_status qb_extract(qb_problem P, qb_batch b, const uint8_t *X_d, const int32_t
  * the groups run concurrently (side streams joined back into `stream`),
  * largest first.  The tile must be symmetric (as qb_extract writes it).
  * Capacity: 1 <= R <= 16, 1 <= B <= 16, nsw >= 1, inst_base + J <= 2^28.
- * Where a replica's sweep is spread over several waves of a workgroup, the
+ * Where a replica's sweep is spread over several waves of a workgroup that
+ * take accepts one by one (QB_ANNEAL_MULTI_WAVE), the
  * waves wait on each other with bounded waits (qb_set_anneal_wait_limit); a
  * replica whose wait runs out (never seen at the default limit) reports
  * e = INT64_MIN, so every launch completes. */
@@ -306,7 +312,8 @@ qb_status qb_anneal(qb_batch b, const void *tile_d, int32_t int8_tile, const int
  * annealers (qb_anneal): a wave that reads a list word `polls` times without
  * finding it written gives up, and its replica reports e = INT64_MIN (Y then
  * holds an unfinished state).  Default 2^24 polls (about a second); 0 makes
- * every wait that does not succeed at once give up.  Process-wide, takes
+ * every wait that does not succeed at once give up.  While the limit is not
+ * the default, QB_ANNEAL_AUTO takes those kernels.  Process-wide, takes
  * effect at the next launch; for tests of that path.  QB_E_ARG if polls < 0. */
 qb_status qb_set_anneal_wait_limit(int32_t polls);
 

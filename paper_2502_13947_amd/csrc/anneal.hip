@@ -1,6 +1,10 @@
 // Sub-QUBO extraction (eq. 4, sub-QUBO construction in Alg. 3), the batched
 // Ising-machine stage and the write-back of Alg. 3 on gfx950.
 //
+// The automatic choice of annealer is the speculating kernel of
+// anneal_spec.hip; the kernels here take accepts one by one, and serve R >= 4
+// replicas of many jobs, plans that name them, and bounded waits.
+//
 // Annealer layout (the one-wave kernel; the multi-wave kernels below spread
 // the same sweep over several waves): one replica per wave64, the R
 // replicas of a job share a workgroup and its tile.  Lane L owns positions
@@ -1225,28 +1229,42 @@ __global__ void k_reset_queues(int *__restrict__ q, int n)
     if ((int)threadIdx.x < n) q[threadIdx.x] = 0;
 }
 
+// Whether the speculating kernel is the automatic choice.  It takes a job's
+// sweep 2.5 to 3 times as fast as the other kernels (m = 64, 128, 256, 512,
+// 1024, 256 jobs, R = 1, int8: 0.5, 0.8, 1.5, 2.9, 8 us a sweep against 1.5,
+// 1.9, 3.4, 6.7, 23), but with a workgroup of its own for every replica; the
+// one-wave kernels pack the R replicas of a job into one workgroup and, once
+// R replicas of many jobs fill the chip several times over, finish more
+// replicas a microsecond (m = 300, 256 jobs x 16: 12.6 us a sweep for all
+// against 26).  The lines, in replicas per compute unit, lie where both took
+// the same time.  At mp = 1024 it takes 170 us to load the columns (256
+// jobs; 84 us before the others' first sweep), which 8 sweeps win back.
+bool spec_pays(int cls, bool int8_tile, int njobs, int R, int nsw)
+{
+    static const int per_cu[2][QB_NCLASS] = {{0, 2, 6, 8, 12}, {4, 5, 8, 12, 12}};
+    int ncu = 0;
+    if (cls == 0 && nsw < 8) return false;
+    if (R < 4 || qb_cu_count(&ncu) != hipSuccess) return true;
+    int lim = per_cu[int8_tile ? 1 : 0][cls];
+    if (int8_tile && cls == 1 && R == 4) lim = 3;      // four replicas still fit the multi-wave kernel
+    return (int64_t)njobs * R <= (int64_t)lim * ncu;
+}
+
 bool dispatch_anneal(int cls, bool int8_tile, int nblocks, int R, hipStream_t s, const int32_t *jobs, qb_batch b,
                      const void *tiles, const int32_t *F0, const uint8_t *y0, int nsw, int B, const int32_t *thr,
                      uint64_t seed, uint32_t inst_base, const qb_iter *it, uint8_t *Y, int64_t *e)
 {
+    const int want = b->plan.kernel[cls];
+    // (rows in global memory: the one class whose multi-wave kernel reads them there)
+    const bool global_rows = cls == (int8_tile ? 0 : 1);
+    if ((want == QB_ANNEAL_AUTO || (want == QB_ANNEAL_MULTI_WAVE_GLOBAL && !global_rows)) &&
+        g_wait_limit.load(std::memory_order_relaxed) == MW_WAIT_DEFAULT && spec_pays(cls, int8_tile, nblocks, R, nsw) &&
+        qb_launch_anneal_spec(cls, int8_tile, nblocks, R, s, jobs, b, tiles, F0, y0, nsw, B, thr, seed, inst_base, it,
+                              Y, e))
+        return true;
 #define QB_ARGS nblocks, R, s, jobs, b, tiles, F0, y0, nsw, B, thr, seed, inst_base, it, Y, e
-    // the multi-wave kernel with rows in global memory, where the plan asks for it
-    if (b->plan.kernel[cls] == QB_ANNEAL_MULTI_WAVE_GLOBAL) {
-        if (int8_tile) {
-            switch (cls) {
-            case 1: if (launch_anneal_mw_g<8, int8_t>(QB_ARGS)) return true; break;
-            case 2: if (launch_anneal_mw_g<4, int8_t>(QB_ARGS)) return true; break;
-            case 3: if (launch_anneal_mw_g<2, int8_t>(QB_ARGS)) return true; break;
-            }
-        } else {
-            switch (cls) {
-            case 2: if (launch_anneal_mw_g<4, int16_t>(QB_ARGS)) return true; break;
-            case 3: if (launch_anneal_mw_g<2, int16_t>(QB_ARGS)) return true; break;
-            }
-        }
-    }
     // the one-wave kernel with the couplings in registers, where the plan asks for it
-    if (b->plan.kernel[cls] == QB_ANNEAL_ONE_WAVE_REG) {
+    if (want == QB_ANNEAL_ONE_WAVE_REG) {
         if (int8_tile) {
             switch (cls) {
             case 1: if (launch_anneal_dc<8, int8_t, 1>(QB_ARGS)) return true; break;
@@ -1262,14 +1280,14 @@ bool dispatch_anneal(int cls, bool int8_tile, int nblocks, int R, hipStream_t s,
         }
     }
     // the multi-wave kernel where its replicas fit one workgroup
-    if (b->plan.kernel[cls] != QB_ANNEAL_ONE_WAVE && int8_tile) {
+    if (want != QB_ANNEAL_ONE_WAVE && int8_tile) {
         switch (cls) {
         case 0: if (launch_anneal_mw_g<16, int8_t>(QB_ARGS)) return true; break;
         case 1: if (launch_anneal_mw<8, int8_t, 1>(QB_ARGS)) return true; break;
         case 2: if (launch_anneal_mw<4, int8_t, 0>(QB_ARGS)) return true; break;
         case 3: if (launch_anneal_mw<2, int8_t, 0>(QB_ARGS)) return true; break;
         }
-    } else if (b->plan.kernel[cls] != QB_ANNEAL_ONE_WAVE) {
+    } else if (want != QB_ANNEAL_ONE_WAVE) {
         switch (cls) {
         case 1: if (launch_anneal_mw_g<8, int16_t>(QB_ARGS)) return true; break;
         case 2: if (launch_anneal_mw<4, int16_t, 0>(QB_ARGS)) return true; break;
@@ -1375,7 +1393,7 @@ qb_status qb_anneal_x(qb_batch b, const void *tile_d, int32_t int8_tile, const i
         }
         // persistent: a grid of workgroups pulls the class's jobs from its queue
         b->lq = persist ? b->queue_d + c : nullptr;
-        b->lgrid = persist ? std::min(nblk, std::max(1, ncu * b->plan.wgs_per_cu)) : 0;
+        b->lgrid = persist ? std::max(1, ncu * b->plan.wgs_per_cu) : 0;
         const int32_t *order = (b->plan.lpt ? b->lpt_d : b->iord_d) + b->cls_begin[c];
         const bool ok = dispatch_anneal(c, int8_tile != 0, nblk, R, ls, order, b, tile_d, F0_d, y0_d, nsw, B, thr_d,
                                         seed, inst_base, it, Y_d, e_d);

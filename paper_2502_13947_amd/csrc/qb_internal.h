@@ -153,7 +153,7 @@ struct qb_batch_s {
     int32_t *iord_d = nullptr;        // [J] jobs by class, then job index (the queue order without LPT)
     int *queue_d = nullptr;           // [QB_NCLASS] job counters of the persistent annealer
     int *lq = nullptr;                // launch in progress: its class's counter (persistent) or null
-    int lgrid = 0;                    // launch in progress: persistent grid (0: one workgroup per job)
+    int lgrid = 0;                    // launch in progress: persistent grid (0: one workgroup per job or replica)
     int32_t *dboff_d = nullptr;       // [J] first diagonal block of each job (sparse tiles)
     int64_t dblk_words = 0;           // words of all jobs' int8 diagonal blocks (1024 per block)
     bool dblk_valid = false;          // the last sparse extraction wrote the diagonal blocks
@@ -194,8 +194,15 @@ qb_status qb_trace_x(qb_batch b, int32_t R, const uint16_t *F_d, const uint8_t *
                      const uint8_t *y0_d, uint16_t *outF_d, uint8_t *outL_d, const qb_iter *it, int64_t cap,
                      void *stream);
 
-// Workgroups of an annealer launch: the persistent grid, else one per job.
-static inline int qb_grid(const qb_batch_s *b, int njobs) { return b->lgrid ? b->lgrid : njobs; }
+// Workgroups of an annealer launch: the persistent grid (at most one per
+// job), else one per job.
+static inline int qb_grid(const qb_batch_s *b, int njobs)
+{
+    return b->lgrid && b->lgrid < njobs ? b->lgrid : njobs;
+}
+bool qb_launch_anneal_spec(int cls, bool int8_tile, int njobs, int R, hipStream_t s, const int32_t *jobs, qb_batch b,
+                           const void *tiles, const int32_t *F0, const uint8_t *y0, int nsw, int B, const int32_t *thr,
+                           uint64_t seed, uint32_t inst_base, const qb_iter *it, uint8_t *Y, int64_t *e);
 // Compute units of the current device (cached per device).
 hipError_t qb_cu_count(int *out);
 
