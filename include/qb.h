@@ -324,8 +324,9 @@ qb_status qb_set_anneal_wait_limit(int32_t polls);
  * one.  For a problem with |Q| <= 127 the jobs' diagonal 64 x 64 blocks
  * follow the rows as int8 (dblk_words = 1024 words per block, qb_tile_ms(m)
  * blocks per job in job order; byte [block][L][k] = T[64 b + k][64 b + L],
- * zero outside the job), which qb_anneal_ell keeps in registers.  The
- * buffer holds off[J]*W + dblk_words words, 16-byte aligned. */
+ * zero outside the job), for callers that want them dense (qb_anneal_ell
+ * reads the rows only).  The buffer holds off[J]*W + dblk_words words,
+ * 16-byte aligned. */
 qb_status qb_extract_ell(qb_problem P, qb_batch b, const uint8_t *X_d, const int32_t *H_d, uint32_t *tile_d,
                          int32_t *c_d, int32_t *F0_d, uint8_t *y0_d, void *stream);
 /* qb_anneal on ELL tiles (qb_extract_ell, width W): the same sweep, the same

@@ -2,20 +2,20 @@
 // construction in Alg. 3) and the batched Ising-machine stage of Alg. 3 on it,
 // on gfx950.
 //
-// The annealer is the dense kernel's ballot-block sweep with the same
-// random numbers and thresholds, so Y and e are bit-identical to it: lane L
-// owns positions 64*s + L, a block's 64 candidates are evaluated at once and
-// the lowest accepting lane k is taken (ballot + find-first-set), after
-// which only lanes past k re-evaluate.  What differs is where the fields
-// live and how an accept updates them.  Row k of a sparse tile has a handful
-// of entries, so instead of every lane adding its slice of a dense row, the
-// flip bases F of each replica live in LDS and lane t adds the t-th entry of
-// row k to F[col_t] with one LDS atomic add (the entries of a row have
-// distinct columns); the current block's F is read back before the next
-// ballot, together with the row of the next lane that accepted in the
-// current ballot (most often the next accept).  The job's ELL tile is staged
-// in LDS once and shared by the rw replicas (waves) of the workgroup; rw only
-// changes the schedule.
+// The annealer takes the dense kernel's random numbers and thresholds, so Y
+// and e are bit-identical to it: lane L owns positions 64*s + L.  What
+// differs is where the fields live and how an accept updates them.  Row k of
+// a sparse tile has a handful of entries, so instead of every lane adding its
+// slice of a dense row, the flip bases F of each replica live in LDS and an
+// accepted row's entries are added there by LDS atomic adds.  The job's ELL
+// tile is staged in LDS once and shared by the rw replicas (waves) of the
+// workgroup; rw only changes the schedule.
+//
+// k_anneal_ell_spec decides a whole sweep at once and repairs it;
+// k_anneal_ell takes accepts one by one (a block's 64 candidates evaluated at
+// once, the lowest accepting lane taken by ballot and find-first-set, lanes
+// past it re-evaluated after its row was added), and serves the jobs that do
+// not leave LDS for the other's tables, and rows wider than 255.
 #include "qb_internal.h"
 
 namespace {
@@ -218,217 +218,252 @@ __global__ void __launch_bounds__(1024) k_anneal_ell(const int32_t *__restrict__
     if (acnt && lane == 0) acnt[(size_t)q * R + r] = nacc;
 }
 
-// The same sweep with the block's own couplings in registers (int8 tiles,
-// W <= 64).  Lane L holds column L of the current diagonal block, T[64 s +
-// k][64 s + L] for k < 64 (written by the extraction), so an accept moves
-// the block's move values dE = sigma F by a register read -- the dense
-// owner's accept chain, with no LDS access on it.  The F of every position
-// still lives in LDS and still receives every entry of each accepted row by
-// an LDS atomic add, so it is exact at the start of each block; those adds
-// are issued one accept late (the row read overlaps the next accept's
-// chain) and are never read back within the block.  A lane that flips has
-// its sigma negated, but its dE is not read again in the block and the
-// negation commutes with the later updates (the dense kernel's argument).
-// The next block's column is loaded a whole block ahead, into the other of
-// two register sets (even and odd blocks).
-__device__ __forceinline__ int32_t dcol_at(const uint32_t (&d)[16], int k)
-{
-    // v_bfe_i32 takes its offset modulo 32 (bits [4:0]), so 8 k selects
-    // byte k & 3 without a mask
-    return __builtin_amdgcn_sbfe((int)d[k >> 2], (uint32_t)k * 8u, 8u);
-}
+// The same sweep, speculated: a whole sweep is decided at once and repaired
+// until it agrees with the sequential one (the fixed point of evaluating
+// every position against a guess of all decisions is the sequential sweep's,
+// as a position's answer depends on lower positions only).  A row of a sparse
+// tile reaches few positions, so almost every first guess is right: on the
+// sub-QUBOs of the n = 20000 workload (1024 variables, 230 accepts a sweep)
+// 2.8 rounds change anything, against a chain of 230 accepts.
+//
+// One wave per replica, lane L holding the positions 64 s + L.  F lives in
+// LDS.  A round compares every position's field with its threshold and adds
+// what the changed decisions make of the fields of *later* positions (LDS
+// atomic adds); once nothing changes, the accepted rows' entries at earlier
+// positions are added too.  Entries ascend by column, so a row's earlier part
+// comes first; of either part the first entry is in registers, and the others
+// are read from the tile in LDS by the few lanes that have any.  With F exact
+// at both ends the energy of the whole run is 1/2 sum (y - y0) (F0 + F): no
+// sweep sums it.  The thresholds of KT sweeps at a time are staged in LDS (KT
+// = 0: read from memory), one barrier per KT sweeps.
+//
+// Bound by a wave's own instructions and LDS round trips (12,000 cycles a
+// sweep of 1024, Philox 2200 of them; 16 replicas take as long as one).
+// Measured, 128 jobs x 16 replicas x 1000 sweeps: 5.1 ms, against 30.2 ms for
+// a kernel that chained the accepts one by one with the block's couplings in
+// registers.
+__device__ __forceinline__ int32_t sat_add(int32_t a, int32_t b) { return __builtin_elementwise_add_sat(a, b); }
 
-__device__ __forceinline__ void load_dcol(uint32_t (&d)[16], const uint8_t *__restrict__ src)
+template <int MS, bool TLDS>
+__global__ void __launch_bounds__(512) k_anneal_ell_spec(const int32_t *__restrict__ jobs, int rgroups,
+                                                         const int32_t *__restrict__ off, int W,
+                                                         const uint32_t *__restrict__ tiles,
+                                                         const int32_t *__restrict__ F0,
+                                                         const uint8_t *__restrict__ y0, int nsw, int B,
+                                                         const int32_t *__restrict__ thr, int KT, int R, int rw,
+                                                         uint32_t k0, uint32_t k1, uint32_t inst_base,
+                                                         const qb_iter *__restrict__ it, uint8_t *__restrict__ Y,
+                                                         int64_t *__restrict__ eout, int32_t *__restrict__ acnt)
 {
-    const uint4 *v = reinterpret_cast<const uint4 *>(src);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint4 t = v[i];
-        d[4 * i + 0] = t.x;
-        d[4 * i + 1] = t.y;
-        d[4 * i + 2] = t.z;
-        d[4 * i + 3] = t.w;
-    }
-}
-
-template <int MS>
-__global__ void __launch_bounds__(512) k_anneal_ell_dc(const int32_t *__restrict__ jobs, int rgroups,
-                                                        const int32_t *__restrict__ off, int W,
-                                                        const uint32_t *__restrict__ tiles,
-                                                        const uint8_t *__restrict__ dblk,
-                                                        const int32_t *__restrict__ dboff,
-                                                        const int32_t *__restrict__ F0,
-                                                        const uint8_t *__restrict__ y0, int nsw, int B,
-                                                        const int32_t *__restrict__ thr, int R, int rw, uint32_t k0,
-                                                        uint32_t k1, uint32_t inst_base,
-                                                        const qb_iter *__restrict__ it, uint8_t *__restrict__ Y,
-                                                        int64_t *__restrict__ eout, int32_t *__restrict__ acnt)
-{
-    constexpr int MP = 64 * MS;
+    constexpr int MP = 64 * MS, NPRE = 8;
     extern __shared__ __align__(16) uint32_t dl[];
     const int q = jobs[blockIdx.x / rgroups];
     const int rg = blockIdx.x % rgroups;
     const int base = off[q], m = off[q + 1] - base;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = rg * rw + wid;
+    const bool live = r < R;
 
-    // Per wave MP fields and then 64 dump words: dump word L (F[MP + L])
-    // holds the ELL word (column MP + L, value 0) and only ever receives
-    // zeros.  A padding word at position w of a staged row becomes that same
-    // word for column MP + w, so every lane adds its row word without a
-    // branch or mask: a padding word, or a lane past the row reading its own
-    // dump word, adds zero into its own dump word (no two lanes share one).
-    uint32_t *tl = dl;                                   // [m][W]
-    int32_t *F = reinterpret_cast<int32_t *>(dl + (size_t)MP * W) + wid * (MP + 64);
+    uint32_t *tl = dl;                                            // [MP][W]
+    int32_t *Fall = reinterpret_cast<int32_t *>(dl + (size_t)MP * W);   // [rw][MP]
+    int32_t *F = Fall + wid * MP;
+    int32_t *ts = Fall + rw * MP;                                 // [2][KT][2^B]
+    uint16_t *info = reinterpret_cast<uint16_t *>(ts + (TLDS ? (size_t)2 * KT << B : 0));   // [MP] entries: earlier, all
     {
-        const uint32_t *src = tiles + (int64_t)base * W;
-        const int nw = m * W;
-        for (int t = tid; t < nw; t += blockDim.x) {
-            const uint32_t v = src[t];
-            tl[t] = v != 0u ? v : (uint32_t)(MP + t % W);
+        const uint4 *src = reinterpret_cast<const uint4 *>(tiles + (int64_t)base * W);
+        uint4 *dst = reinterpret_cast<uint4 *>(tl);
+        const int n16 = m * W / 4;
+        for (int t = tid; t < n16; t += nt) dst[t] = src[t];
+        if constexpr (TLDS) {
+            const int n = min(KT, nsw) << B;
+            for (int t = tid; t < n; t += nt) ts[t] = thr[t];
         }
     }
-#pragma unroll
-    for (int s = 0; s < MS; ++s) {
-        const int pos = 64 * s + lane;
-        F[pos] = pos < m ? F0[base + pos] : 0;
-    }
-    F[MP + lane] = MP + lane;
     __syncthreads();
-    if (r >= R) return;   // no barrier follows
-
-    const uint8_t *dq = dblk + (size_t)dboff[q] * DBLK_BYTES + lane * 64;
-    // byte offset of a row word in LDS: row_offset * rsel + rbase, with rsel =
-    // 1 and rbase = 4 L for a lane L < W, else rsel = 0 and rbase the lane's
-    // dump word (row offsets stay below 1024 * 64 * 4 < 2^24, the range of
-    // the 24-bit multiply)
-    uint32_t rsel = lane < W ? 1u : 0u;
-    asm volatile("" : "+v"(rsel));   // opaque: one multiply-add, not a select
-    const uint32_t rbase = lane < W ? 4u * (uint32_t)lane
-                                    : (uint32_t)(reinterpret_cast<const char *>(F + MP + lane) -
-                                                 reinterpret_cast<const char *>(dl));
-    uint32_t ybits = 0;
+    for (int a = tid; a < MP; a += nt) {
+        int nu = 0, cnt = 0;
+        if (a < m)
+            for (int t = 0; t < W; ++t) {
+                const uint32_t wd = tl[a * W + t];
+                if (wd == 0u) continue;
+                cnt = t + 1;
+                if (qb_ell_col(wd) < a) nu = t + 1;
+            }
+        info[a] = (uint16_t)(nu | (cnt << 8));
+    }
+    int32_t M[MS];                          // -y
+    uint32_t yb = 0;
 #pragma unroll
     for (int s = 0; s < MS; ++s) {
         const int pos = 64 * s + lane;
-        if (pos < m && y0[base + pos]) ybits |= 1u << s;
+        if (live) F[pos] = pos < m ? F0[base + pos] : 0;
+        if (pos < m && y0[base + pos]) yb |= 1u << s;
+        M[s] = (yb >> s) & 1u ? -1 : 0;
     }
-    int64_t e = 0;
+    const uint32_t y00 = yb;
+    __syncthreads();
+
+    // first entries: twice the coupling, and the byte offset of the field it
+    // moves (none: zero into the position's own field)
+    const uint32_t fo = (uint32_t)(reinterpret_cast<char *>(F) - reinterpret_cast<char *>(dl));
+    int32_t dv[MS], uv[MS];
+    uint32_t da[MS], ua[MS];
+    uint32_t hd = 0, hd2 = 0, hu = 0, hu2 = 0;   // positions with one, and with more, later or earlier entries
+#pragma unroll
+    for (int s = 0; s < MS; ++s) {
+        const int pos = 64 * s + lane;
+        const int nu = info[pos] & 255, nd = (info[pos] >> 8) - nu;
+        const uint32_t wu = nu > 0 ? tl[pos * W] : 0u, wd = nd > 0 ? tl[pos * W + nu] : 0u;
+        uv[s] = 2 * qb_ell_val(wu);
+        ua[s] = fo + 4u * (uint32_t)(nu > 0 ? qb_ell_col(wu) : pos);
+        dv[s] = 2 * qb_ell_val(wd);
+        da[s] = fo + 4u * (uint32_t)(nd > 0 ? qb_ell_col(wd) : pos);
+        hu |= (uint32_t)(nu > 0) << s;
+        hu2 |= (uint32_t)(nu > 1) << s;
+        hd |= (uint32_t)(nd > 0) << s;
+        hd2 |= (uint32_t)(nd > 1) << s;
+    }
+    auto field = [&](uint32_t o) { return reinterpret_cast<int32_t *>(reinterpret_cast<char *>(dl) + o); };
+    // adds the first entries of the positions `who`, with the signs `neg`;
+    // the other positions add zero, which takes no branch
+    auto scatter = [&](uint32_t who, uint32_t neg, const int32_t (&v)[MS], const uint32_t (&at)[MS]) {
+#pragma unroll
+        for (int s = 0; s < MS; ++s) {
+            const int32_t n = __builtin_amdgcn_sbfe((int)neg, s, 1), on = __builtin_amdgcn_sbfe((int)who, s, 1);
+            atomicAdd(field(at[s]), ((v[s] ^ n) - n) & on);
+        }
+    };
+    // adds entries from the tile, of the few lanes that have any: the earlier
+    // or the later ones but for `skip`
+    auto scatter_rows = [&](uint32_t who, uint32_t neg, bool later, int skip) {
+        while (who) {
+            const int s = __builtin_ctz(who);
+            who &= who - 1;
+            const int pos = 64 * s + lane;
+            const int nu = info[pos] & 255, cnt = info[pos] >> 8;
+            const int32_t f = (neg >> s) & 1u ? -2 : 2;
+            const uint32_t *row = tl + pos * W;
+            for (int t = (later ? nu : 0) + skip; t < (later ? cnt : nu); ++t) {
+                const uint32_t wd = row[t];
+                atomicAdd(F + qb_ell_col(wd), f * qb_ell_val(wd));
+            }
+        }
+    };
+
     int32_t nacc = 0;
     const uint32_t tag = (1u << 28) | (inst_base + (it ? it->inst : 0u) + (uint32_t)q);
     constexpr int G = (MS + 3) / 4;
     const int sh = 32 - B;
-    const int nblk = (m + 63) >> 6;                      // blocks with positions
-    // the columns of the even and of the odd blocks: once block s is done,
-    // its set is refilled with block s + 2 (in sweep order), a whole block
-    // ahead of its use.  An odd block count is padded with one block without
-    // positions, so that a block's parity, and with it its set, is the same
-    // in every sweep.  With one block the column never changes.
-    uint32_t cA[16], cB[16];
-    const int nbe = nblk + (nblk & 1);
-    load_dcol(cA, dq);
-    if (MS > 1 && nblk > 1) load_dcol(cB, dq + DBLK_BYTES);
-    auto thresholds = [&](int sw, int32_t (&tv)[MS]) {
+    const int chunk = TLDS ? KT : nsw;
+    for (int c0 = 0; c0 < nsw; c0 += chunk) {
+        const int nc = min(chunk, nsw - c0), buf = TLDS ? (c0 / chunk) & 1 : 0;
+        // the next chunk's thresholds, on their way while this one is swept
+        int32_t pre[NPRE];
+        const int nn = TLDS ? max(min(chunk, nsw - c0 - nc), 0) << B : 0;
+        if constexpr (TLDS) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const uint4 o = qb_philox(make_uint4(((uint32_t)g << 6) | (uint32_t)lane, (uint32_t)sw, (uint32_t)r, tag),
-                                      k0, k1);
-            const int32_t *ts = thr + ((size_t)sw << B);
-#pragma unroll
-            for (int w = 0; w < 4; ++w)
-                if (4 * g + w < MS) tv[4 * g + w] = ts[qb_word(o, w) >> sh];
+            for (int i = 0; i < NPRE; ++i)
+                if (tid + i * nt < nn) pre[i] = thr[((size_t)(c0 + nc) << B) + tid + i * nt];
         }
-    };
-    int32_t tvn[MS];
-    thresholds(0, tvn);
-    // F of the next block, read as soon as the block before it has issued
-    // its last add (every earlier atomic add of this wave precedes the read,
-    // so it is exact), so that its latency overlaps that block's bookkeeping
-    int32_t fsn = F[lane];
-
-    for (int sw = 0; sw < nsw; ++sw) {
-        int32_t tv[MS];
+        if (live) {
+#pragma unroll 1
+            for (int sw = c0; sw < c0 + nc; ++sw) {
+                int32_t tp[MS];
 #pragma unroll
-        for (int s = 0; s < MS; ++s) tv[s] = tvn[s];
-        if (sw + 1 < nsw) thresholds(sw + 1, tvn);
+                for (int g = 0; g < G; ++g) {
+                    const uint4 o = qb_philox(make_uint4(((uint32_t)g << 6) | (uint32_t)lane, (uint32_t)sw, (uint32_t)r,
+                                                         tag), k0, k1);
 #pragma unroll
-        for (int s = 0; s < MS; ++s) {
-            if (s < nblk) {
-            const int na = min(m - 64 * s, 64);
-            const uint32_t(&dc)[16] = (s & 1) ? cB : cA;
-            const int32_t fs = fsn;
-            const int32_t M0 = ((ybits >> s) & 1u) ? -1 : 0;
-            const int32_t s2 = M0 ? -2 : 2, ns2 = -s2;   // 2 sigma
-            int32_t dE = (fs ^ M0) - M0;
-            // y of the block's lanes at its start: a lane accepts at most once
-            // in the block, so an accepted lane's y is still this bit
-            const uint64_t ym0 = __ballot(M0 != 0);
-            uint64_t amask = 0;        // lanes accepted in the block
-            int32_t eb = 0;            // their dE: at most 64 moves of |dE| < 2^24
-            // the lane's threshold while it may still accept in the block: a
-            // lane past the block, or at or below the last accept, gets
-            // INT32_MIN, which no dE reaches (|dE| < 2^24), so the ballot
-            // needs no mask of pending lanes
-            int32_t tk = lane < na ? tv[s] : INT32_MIN;
-            uint64_t acc = __ballot(dE <= tk);
-            // the previous accept's row word and factor (a lane's own dump
-            // word before the first accept); its adds are issued one accept
-            // late, so the read is not waited for on the accept chain
-            uint32_t pwr = (uint32_t)(MP + lane);
-            int32_t pd2 = 0;
-            while (acc) {
-                const int k = __builtin_ctzll(acc);
-                const uint64_t bk = 1ull << k;
-                eb += __builtin_amdgcn_readlane(dE, k);
-                amask |= bk;
-                int32_t f, d2, yk;
-                qb_accept_sign<false>(ym0, k, s2, ns2, f, d2, yk);
-                dE += __mul24(f, dcol_at(dc, k));
-                tk = lane <= k ? INT32_MIN : tk;
-                const uint64_t accn = __ballot(dE <= tk);
-                // the chain of this accept is done: only now wait for the
-                // previous accept's row word and add it, then read this one's
-                __builtin_amdgcn_sched_barrier(0);
-                atomicAdd(&F[qb_ell_col(pwr)], __mul24(pd2, qb_ell_val(pwr)));
-                // row word of lane L < W, else the lane's dump word
-                pwr = *reinterpret_cast<const uint32_t *>(
-                    reinterpret_cast<const char *>(dl) +
-                    __umul24((uint32_t)((64 * s + k) * W * 4), rsel) + rbase);
-                pd2 = d2;
-                acc = accn;
+                    for (int w = 0; w < 4; ++w)
+                        if (4 * g + w < MS) {
+                            const uint32_t k = qb_word(o, w) >> sh;
+                            tp[4 * g + w] = TLDS ? ts[((buf * KT + sw - c0) << B) + k] : thr[((size_t)sw << B) + k];
+                        }
+                }
+                // dE <= t on x = F ^ -y: for y = 1, -F <= t is ~F <= t - 1 (no
+                // field reaches INT32_MAX, nor a position past the job INT32_MIN)
+#pragma unroll
+                for (int s = 0; s < MS; ++s) tp[s] = 64 * s + lane < m ? sat_add(tp[s], M[s]) : INT32_MIN;
+                auto decide = [&]() {
+                    uint32_t a = 0;
+#pragma unroll
+                    for (int s = MS - 1; s >= 0; --s) a = 2 * a + (uint32_t)((F[64 * s + lane] ^ M[s]) <= tp[s]);
+                    return a;
+                };
+                uint32_t acc = decide();
+                scatter(acc & hd, yb, dv, da);
+                scatter_rows(acc & hd2, yb, true, 1);
+                while (true) {
+                    const uint32_t a = decide();
+                    const uint32_t t = (a ^ acc) & hd;
+                    acc = a;
+                    if (__ballot(t != 0u) == 0) break;
+                    // the other way where no longer accepted from 0, or accepted from 1
+                    scatter_rows(t, a ^ ~yb, true, 0);
+                }
+                scatter(acc & hu, yb, uv, ua);
+                scatter_rows(acc & hu2, yb, false, 1);
+                nacc += __builtin_popcount(acc);
+                yb ^= acc;
+#pragma unroll
+                for (int s = 0; s < MS; ++s) M[s] = -(int32_t)((yb >> s) & 1u);
             }
-            atomicAdd(&F[qb_ell_col(pwr)], __mul24(pd2, qb_ell_val(pwr)));
-            fsn = F[64 * (s + 1 < nblk ? s + 1 : 0) + lane];
-            e += eb;
-            nacc += __builtin_popcountll(amask);
-            const uint32_t yb = (uint32_t)((ym0 ^ amask) >> lane) & 1u;
-            ybits = (ybits & ~(1u << s)) | (yb << s);
-            }
-            if (MS > 1 && s < nbe) {
-                int t = s + 2;
-                if (t >= nbe) t -= nbe;
-                if (t < nblk) load_dcol((s & 1) ? cB : cA, dq + (size_t)t * DBLK_BYTES);
+        }
+        if constexpr (TLDS) {
+            if (nn > 0) {
+                int32_t *dst = ts + ((size_t)((buf ^ 1) * KT) << B);
+#pragma unroll
+                for (int i = 0; i < NPRE; ++i)
+                    if (tid + i * nt < nn) dst[tid + i * nt] = pre[i];
+                for (int t = tid + NPRE * nt; t < nn; t += nt) dst[t] = thr[((size_t)(c0 + nc) << B) + t];
+                __syncthreads();
             }
         }
     }
+    if (!live) return;
 
     uint8_t *Yr = Y + (size_t)base * R + (size_t)r * m;
+    int64_t e = 0;
 #pragma unroll
     for (int s = 0; s < MS; ++s) {
         const int pos = 64 * s + lane;
-        if (pos < m) Yr[pos] = (uint8_t)((ybits >> s) & 1u);
+        if (pos < m) {
+            const int y = (int)((yb >> s) & 1u), d = y - (int)((y00 >> s) & 1u);
+            Yr[pos] = (uint8_t)y;
+            e += (int64_t)d * ((int64_t)F0[base + pos] + F[pos]);
+        }
     }
-    if (lane == 0) eout[(size_t)q * R + r] = e;
-    if (acnt && lane == 0) acnt[(size_t)q * R + r] = nacc;
+    e = qb_wave_sum_i64(e) / 2;
+    const int64_t na = acnt ? qb_wave_sum_i64(nacc) : 0;
+    if (lane == 0) {
+        eout[(size_t)q * R + r] = e;
+        if (acnt) acnt[(size_t)q * R + r] = (int32_t)na;
+    }
 }
 
 constexpr size_t LDS_MAX = 160 * 1024;
 
-// The job's ELL tile, each replica's fields, and 64 words per replica (the
-// register-block kernel's dump area).
+// The LDS of a workgroup that the entry point admits: the job's ELL tile,
+// each replica's fields, and 64 words per replica.
 inline size_t ell_lds_bytes(int ms, int W, int rw)
 {
     return sizeof(uint32_t) * ((size_t)64 * ms * (W + rw) + (size_t)64 * rw);
+}
+
+// Sweeps whose thresholds the speculating kernel stages at a time: as many as
+// fit (at most 4), 0 to read them from memory; -1 where the job's rows, the
+// fields and the entry counts do not fit.
+inline int ell_spec_stage(int ms, int W, int rw, int B, size_t *bytes)
+{
+    const size_t need = sizeof(uint32_t) * ((size_t)64 * ms * (W + rw)) + sizeof(uint16_t) * 64 * ms;
+    for (int k = 4; k >= 0; k >>= 1) {
+        *bytes = need + (B <= 12 ? ((size_t)2 * k * sizeof(int32_t)) << B : 0);
+        if (k > 0 && B > 12) continue;
+        if (*bytes <= LDS_MAX) return k;
+        if (k == 0) break;
+    }
+    return -1;
 }
 
 template <int MS>
@@ -437,18 +472,17 @@ qb_status launch_ell(int njobs, int rw, int R, hipStream_t s, const int32_t *job
                      uint64_t seed, uint32_t inst_base, const qb_iter *it, uint8_t *Y, int64_t *e)
 {
     const size_t lds = ell_lds_bytes(MS, W, rw);
-    if (b->dblk_valid && W <= 64 && rw <= 8) {
-        // the extraction wrote the int8 diagonal blocks after the ELL rows
-        // (at most 8 replicas per workgroup: up to 256 registers per lane
-        // hold the two column sets; beyond, the in-LDS kernel, same result)
-        QB_TRY_HIP(hipFuncSetAttribute((const void *)k_anneal_ell_dc<MS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)LDS_MAX));
-        const int rgroups = (R + rw - 1) / rw;
-        const uint8_t *dblk = reinterpret_cast<const uint8_t *>(tiles + (int64_t)b->total * W);
-        k_anneal_ell_dc<MS><<<njobs * rgroups, 64 * rw, lds, s>>>(jobs, rgroups, b->off_d, W, tiles, dblk, b->dboff_d,
-                                                                  F0, y0, nsw, B, thr, R, rw, (uint32_t)seed,
-                                                                  (uint32_t)(seed >> 32), inst_base, it, Y, e,
-                                                                  b->acnt_d);
+    size_t slds = 0;
+    // up to 8 replicas per workgroup (256 registers a lane), more in further workgroups
+    const int srw = rw < 8 ? rw : 8;
+    const int kt = W <= 255 ? ell_spec_stage(MS, W, srw, B, &slds) : -1;
+    if (kt >= 0) {
+        const int rgroups = (R + srw - 1) / srw;
+        const auto kern = kt > 0 ? k_anneal_ell_spec<MS, true> : k_anneal_ell_spec<MS, false>;
+        QB_TRY_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX));
+        kern<<<njobs * rgroups, 64 * srw, slds, s>>>(jobs, rgroups, b->off_d, W, tiles, F0, y0, nsw, B, thr, kt, R, srw,
+                                                     (uint32_t)seed, (uint32_t)(seed >> 32), inst_base, it, Y, e,
+                                                     b->acnt_d);
         QB_LAUNCH_CHECK();
         return QB_OK;
     }
@@ -493,7 +527,6 @@ extern "C" qb_status qb_extract_ell(qb_problem P, qb_batch b, const uint8_t *X_d
     uint8_t *dblk = P->int8_ok ? reinterpret_cast<uint8_t *>(tile_d + (int64_t)b->total * P->ellw) : nullptr;
     k_extract_ell<<<b->J, 256, 0, qb_stream(stream)>>>(P->ell, P->ellw, P->ecnt, P->diag, P->n, b->sol_d, b->off_d,
                                                        b->idx_d, X_d, H_d, tile_d, c_d, F0_d, y0_d, dblk, b->dboff_d);
-    b->dblk_valid = dblk != nullptr;
     QB_LAUNCH_CHECK();
     return QB_OK;
 }

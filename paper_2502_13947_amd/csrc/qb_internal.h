@@ -156,7 +156,6 @@ struct qb_batch_s {
     int lgrid = 0;                    // launch in progress: persistent grid (0: one workgroup per job or replica)
     int32_t *dboff_d = nullptr;       // [J] first diagonal block of each job (sparse tiles)
     int64_t dblk_words = 0;           // words of all jobs' int8 diagonal blocks (1024 per block)
-    bool dblk_valid = false;          // the last sparse extraction wrote the diagonal blocks
     hipEvent_t ev_fork = nullptr, ev_join[QB_NCLASS] = {nullptr};
 };
 
