@@ -168,9 +168,9 @@ qb_status qb_keys(qb_problem P, int32_t z, const uint8_t *X_d, const int32_t *T_
 qb_status qb_random_keys(int32_t n, int32_t z, int32_t t, uint64_t seed, int64_t *K_d, void *stream);
 /* order[p][r] = variable of rank r when sorting solution p by (K desc, index
  * asc) (Alg. 3 "highest values in A"; ties to the lower index).  Keys must
- * satisfy |K| < 2^47 (guaranteed by qb_keys).  n <= 16384 sorts in LDS;
- * larger n (up to 65535) sorts indices in place in order_d with only the
- * short strides in LDS. */
+ * satisfy |K| < 2^47 (guaranteed by qb_keys).  n <= 32768 sorts in registers
+ * and LDS; larger n (up to 65535) sorts indices in place in order_d with only
+ * the short strides in LDS. */
 qb_status qb_rank(int32_t n, int32_t z, const int64_t *K_d, int32_t *order_d, void *stream);
 
 /* ---------------------------------------------------------------- jobs
