@@ -261,7 +261,12 @@ __global__ void __launch_bounds__(256) k_gain(int n, int R, const int32_t *__res
 }
 
 // ------------------------------------------------------------------ training
-// Forward and backward of 64 samples per workgroup (one wave).  The three
+// Forward and backward of 64 samples per workgroup.  What bounds it at
+// training batches is one workgroup's chain, not the card (64 workgroups at
+// 4096 samples), so four waves share every stage: 16 units of the first
+// layer, 16 rows of each product, a part of the small sums each, all in the
+// order of one wave (33 us with one wave, 15 us with four, at 4096 samples;
+// the partial sums' reduction with 16 loads in flight 19 -> 4.9 us).  The three
 // 64x64x64 products -- the second layer's forward pass Z2 = H1 W2^T, the
 // backward pass dH1 = dZ2 W2 and the weight gradient dW2 = dZ2^T H1 -- run
 // on the matrix cores (v_mfma_f32_16x16x16_bf16: BF16 operands, FP32
@@ -286,24 +291,27 @@ __device__ __forceinline__ mlp_v4s mlp_ld4(const uint16_t *row, int k)
     return *reinterpret_cast<const mlp_v4s *>(row + k);
 }
 
-__global__ void __launch_bounds__(64) k_mlp_grad(int B, const uint16_t *__restrict__ feat,
-                                                 const uint8_t *__restrict__ label,
-                                                 const uint16_t *__restrict__ W, float *__restrict__ partial,
-                                                 float *__restrict__ lossp)
+__global__ void __launch_bounds__(256) k_mlp_grad(int B, const uint16_t *__restrict__ feat,
+                                                  const uint8_t *__restrict__ label,
+                                                  const uint16_t *__restrict__ W, float *__restrict__ partial,
+                                                  float *__restrict__ lossp)
 {
     __shared__ float xs[64][8], dss[64], ls[64];
-    __shared__ uint64_t m1s[64];
+    __shared__ uint16_t m1s[4][64];                                   // ReLU mask of 16 units each
+    __shared__ float w3f[64];
     __shared__ __align__(16) uint16_t w2b[64][MP64], w2t[64][MP64];   // W2[k][i], W2^T[i][k]
     __shared__ __align__(16) uint16_t h1b[64][MP64], h1t[64][MP64];   // H1[s][i], H1^T[i][s]
     __shared__ __align__(16) uint16_t z2b[64][MP64], z2t[64][MP64];   // hi of dZ2[s][k], of dZ2^T[k][s]
     __shared__ __align__(16) uint16_t z2l[64][MP64], z2tl[64][MP64];  // lo of the same
     __shared__ float h2f[64][65], dz2f[64][65], dz1f[64][65];
-    const int t = threadIdx.x;
+    const int t = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int b = blockIdx.x * 64 + t;
     const bool ok = b < B;
     const int r16 = t & 15, g = t >> 4;
 
-    for (int e = t; e < 64 * 64; e += 64) {
+    if (wv == 0) w3f[t] = bf16_f(W[OW3 + t]);
+#pragma unroll
+    for (int e = threadIdx.x; e < 64 * 64; e += 256) {
         const uint16_t w = W[OW2 + e];
         w2b[e >> 6][e & 63] = w;
         w2t[e & 63][e >> 6] = w;
@@ -321,27 +329,30 @@ __global__ void __launch_bounds__(64) k_mlp_grad(int B, const uint16_t *__restri
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = 0.0f;
     }
+    if (wv == 0) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) xs[t][i] = x[i];
-    // first layer, as in inference (thread = sample)
-    uint64_t m1 = 0;
+        for (int i = 0; i < 8; ++i) xs[t][i] = x[i];
+    }
+    // first layer, as in inference (lane = sample, wave = 16 of the units)
+    uint32_t m1 = 0;
 #pragma unroll
-    for (int k = 0; k < 64; ++k) {
+    for (int kk = 0; kk < 16; ++kk) {
+        const int k = 16 * wv + kk;
         float acc = bf16_f(W[OB1 + k]);
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc = acc + bf16_f(W[OW1 + k * 8 + i]) * x[i];
-        m1 |= (uint64_t)(acc > 0.0f) << k;
+        m1 |= (uint32_t)(acc > 0.0f) << kk;
         const uint16_t hb = bf16_rne(acc > 0.0f ? acc : 0.0f);
         h1b[t][k] = hb;
         h1t[k][t] = hb;
     }
-    m1s[t] = m1;
+    m1s[wv][t] = (uint16_t)m1;
     __syncthreads();
 
     // second layer on the matrix cores: Z2[s][k] = b2[k] + sum_i H1[s][i] W2[k][i];
     // h2 = BF16(relu(Z2)), stored as -0 where Z2 <= 0 (the ReLU mask)
-#pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
+    {
+        const int mi = wv;                           // 16 rows of the product per wave
 #pragma unroll
         for (int ni = 0; ni < 4; ++ni) {
             const float bias = bf16_f(W[OB2 + 16 * ni + r16]);
@@ -357,18 +368,23 @@ __global__ void __launch_bounds__(64) k_mlp_grad(int B, const uint16_t *__restri
                 h2f[16 * mi + 4 * g + r][16 * ni + r16] = z > 0.0f ? bf16_f(bf16_rne(z)) : -0.0f;
             }
         }
+    }
     __syncthreads();
 
-    // output layer, loss and dZ2 (thread = sample)
+    // output layer and loss (lane = sample; every wave its own copy), and dZ2
+    // of 16 units per wave
     {
         float sc = bf16_f(W[OB3]);
-        for (int k = 0; k < 64; ++k) sc = sc + bf16_f(W[OW3 + k]) * h2f[t][k];
+#pragma unroll 16
+        for (int k = 0; k < 64; ++k) sc = sc + w3f[k] * h2f[t][k];
         const float y = ok && label[b] ? 1.0f : 0.0f;
         const float ds = ok ? (1.0f / (1.0f + expf(-sc)) - y) / (float)B : 0.0f;
-        ls[t] = ok ? ((sc > 0.0f ? sc + log1pf(expf(-sc)) : log1pf(expf(sc))) - y * sc) : 0.0f;
-        dss[t] = ds;
-        for (int k = 0; k < 64; ++k) {
-            const float dz2 = __builtin_signbit(h2f[t][k]) ? 0.0f : ds * bf16_f(W[OW3 + k]);
+        if (wv == 0) ls[t] = ok ? ((sc > 0.0f ? sc + log1pf(expf(-sc)) : log1pf(expf(sc))) - y * sc) : 0.0f;
+        if (wv == 0) dss[t] = ds;
+#pragma unroll
+        for (int kk = 0; kk < 16; ++kk) {
+            const int k = 16 * wv + kk;
+            const float dz2 = __builtin_signbit(h2f[t][k]) ? 0.0f : ds * w3f[k];
             dz2f[t][k] = dz2;
             const uint16_t hi = bf16_rne(dz2);
             const uint16_t lo = bf16_rne(dz2 - bf16_f(hi));
@@ -382,8 +398,8 @@ __global__ void __launch_bounds__(64) k_mlp_grad(int B, const uint16_t *__restri
 
     // backward into the first layer on the matrix cores:
     // dH1[s][i] = sum_k dZ2[s][k] W2[k][i], dZ1 = dH1 where the first layer was positive
-#pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
+    {
+        const int mi = wv;                           // 16 rows of the product per wave
 #pragma unroll
         for (int ni = 0; ni < 4; ++ni) {
             mlp_v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -398,14 +414,15 @@ __global__ void __launch_bounds__(64) k_mlp_grad(int B, const uint16_t *__restri
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int sr = 16 * mi + 4 * g + r, ic = 16 * ni + r16;
-                dz1f[sr][ic] = ((m1s[sr] >> ic) & 1ull) ? acc[r] : 0.0f;
+                dz1f[sr][ic] = ((m1s[ni][sr] >> r16) & 1u) ? acc[r] : 0.0f;
             }
         }
+    }
 
     float *out = partial + (int64_t)blockIdx.x * NPARAM;
     // dW2[k][i] = sum_s dZ2[s][k] H1[s][i] on the matrix cores
-#pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
+    {
+        const int mi = wv;                           // 16 rows of the product per wave
 #pragma unroll
         for (int ni = 0; ni < 4; ++ni) {
             mlp_v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -420,49 +437,69 @@ __global__ void __launch_bounds__(64) k_mlp_grad(int B, const uint16_t *__restri
 #pragma unroll
             for (int r = 0; r < 4; ++r) out[OW2 + (16 * mi + 4 * g + r) * 64 + 16 * ni + r16] = acc[r];
         }
+    }
     __syncthreads();
 
-    // the small sums on VALU, over the samples in index order (thread = unit)
-    {
-        float gb2 = 0.0f, gb1 = 0.0f, gw3 = 0.0f, g1[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    // the small sums on VALU, over the samples in index order (lane = unit,
+    // the sums shared out over the waves)
+    if (wv < 2) {
+        float g1[4] = {0, 0, 0, 0};
+#pragma unroll 8
         for (int bb = 0; bb < 64; ++bb) {
             const float d1 = dz1f[bb][t];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) g1[i] = g1[i] + d1 * xs[bb][i];
-            gb2 = gb2 + dz2f[bb][t];
-            gb1 = gb1 + d1;
-            gw3 = gw3 + dss[bb] * h2f[bb][t];
+            for (int i = 0; i < 4; ++i) g1[i] = g1[i] + d1 * xs[bb][4 * wv + i];
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) out[OW1 + t * 8 + i] = g1[i];
+        for (int i = 0; i < 4; ++i) out[OW1 + t * 8 + 4 * wv + i] = g1[i];
+    } else if (wv == 2) {
+        float gb2 = 0.0f, gb1 = 0.0f;
+#pragma unroll 8
+        for (int bb = 0; bb < 64; ++bb) {
+            gb2 = gb2 + dz2f[bb][t];
+            gb1 = gb1 + dz1f[bb][t];
+        }
         out[OB2 + t] = gb2;
         out[OB1 + t] = gb1;
+    } else {
+        float gw3 = 0.0f;
+#pragma unroll 8
+        for (int bb = 0; bb < 64; ++bb) gw3 = gw3 + dss[bb] * h2f[bb][t];
         out[OW3 + t] = gw3;
-    }
-    if (t == 0) {
-        float gb3 = 0.0f, l = 0.0f;
-        for (int bb = 0; bb < 64; ++bb) {
-            gb3 = gb3 + dss[bb];
-            l = l + ls[bb];
+        if (t == 0) {
+            float gb3 = 0.0f, l = 0.0f;
+#pragma unroll 8
+            for (int bb = 0; bb < 64; ++bb) {
+                gb3 = gb3 + dss[bb];
+                l = l + ls[bb];
+            }
+            out[OB3] = gb3;
+            lossp[blockIdx.x] = l;
         }
-        out[OB3] = gb3;
-        lossp[blockIdx.x] = l;
     }
 }
 
-__global__ void k_mlp_reduce(int nblk, const float *__restrict__ partial, const float *__restrict__ lossp, int B,
-                             float *__restrict__ grad, float *__restrict__ loss)
+// The workgroups' sums in order; sixteen loads in flight (the last block's
+// first thread: the loss).
+__global__ void __launch_bounds__(64) k_mlp_reduce(int nblk, const float *__restrict__ partial,
+                                                   const float *__restrict__ lossp, int B, float *__restrict__ grad,
+                                                   float *__restrict__ loss)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    const int k = blockIdx.x * 64 + threadIdx.x;
+    if (blockIdx.x + 1 == gridDim.x) {
+        if (threadIdx.x == 0 && loss) {
+            float l = 0.0f;
+#pragma unroll 16
+            for (int w = 0; w < nblk; ++w) l = l + lossp[w];
+            *loss = l / (float)B;
+        }
+        return;
+    }
     if (k < NPARAM) {
         float g = 0.0f;
+#pragma unroll 16
         for (int w = 0; w < nblk; ++w) g = g + partial[(int64_t)w * NPARAM + k];
         grad[k] = g;
-    }
-    if (k == 0 && loss) {
-        float l = 0.0f;
-        for (int w = 0; w < nblk; ++w) l = l + lossp[w];
-        *loss = l / (float)B;
     }
 }
 
@@ -576,8 +613,8 @@ extern "C" qb_status qb_mlp_grad(int32_t B, const uint16_t *feat_d, const uint8_
     const int nblk = (B + 63) / 64;
     float *partial = (float *)work_d;
     float *lossp = partial + (size_t)nblk * NPARAM;
-    k_mlp_grad<<<nblk, 64, 0, s>>>(B, feat_d, label_d, W_d, partial, lossp);
-    k_mlp_reduce<<<(NPARAM + 255) / 256, 256, 0, s>>>(nblk, partial, lossp, B, grad_d, loss_d);
+    k_mlp_grad<<<nblk, 256, 0, s>>>(B, feat_d, label_d, W_d, partial, lossp);
+    k_mlp_reduce<<<(NPARAM + 63) / 64 + 1, 64, 0, s>>>(nblk, partial, lossp, B, grad_d, loss_d);
     QB_LAUNCH_CHECK();
     return QB_OK;
 }
@@ -629,8 +666,8 @@ extern "C" qb_status qb_mlp_grad_noalloc(int32_t B, const uint16_t *feat_d, cons
     hipStream_t s = qb_stream(stream);
     const int nblk = (B + 63) / 64;
     float *lossp = partial + (size_t)nblk * NPARAM;
-    k_mlp_grad<<<nblk, 64, 0, s>>>(B, feat_d, label_d, W_d, partial, lossp);
-    k_mlp_reduce<<<(NPARAM + 255) / 256, 256, 0, s>>>(nblk, partial, lossp, B, grad_d, loss_d);
+    k_mlp_grad<<<nblk, 256, 0, s>>>(B, feat_d, label_d, W_d, partial, lossp);
+    k_mlp_reduce<<<(NPARAM + 63) / 64 + 1, 64, 0, s>>>(nblk, partial, lossp, B, grad_d, loss_d);
     QB_LAUNCH_CHECK();
     return QB_OK;
 }
