@@ -247,14 +247,6 @@ __device__ __forceinline__ int below_count(uint64_t m)
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// A barrier that orders LDS only: loads from memory stay in flight over it.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // A wave's blocks and its replica's random numbers.
 template <int MS, typename TT>
 struct SpecWave {
@@ -383,7 +375,7 @@ __device__ __forceinline__ void spec_sweeps(SpecWave<MS, TT> &S, const TT *__res
                 asm volatile("" : "+s"(w), "+s"(nb));
                 if (b > MS / 2 && b >= nb) break;
                 if (b > 0 || sw > 0) {
-                    lds_barrier();
+                    qb_lds_barrier();
                     const int bp = b > 0 ? b - 1 : nb - 1;
                     MaskVec<C::I8> v;
 #pragma unroll
@@ -507,7 +499,7 @@ __device__ __forceinline__ void spec_rows(int f, int lane, int nsw, int np, cons
         for (int b = 0; b < NP; ++b) {
             if (b >= np) break;
             if (b > 0 || sw > 0) {
-                lds_barrier();
+                qb_lds_barrier();
                 const uint32_t lo = L.list[par ^ 1][lane], hi = NB > 1 ? L.list[par ^ 1][64 + lane] : 0u;
                 const int cnt = __builtin_amdgcn_readfirstlane(L.cnt[par ^ 1]);
                 for (int i0 = f; i0 < cnt; i0 += U * FW) {
@@ -574,7 +566,7 @@ __device__ __forceinline__ void spec_sweeps_far(SpecWave<MS, TT> &S, const TT *_
             const bool begun = b > 0 || sw > 0;
             // a phase is as long as its settling wave takes: that one first
             if (d == 0 && w < np) __builtin_amdgcn_s_setprio(3);
-            if (begun) lds_barrier();
+            if (begun) qb_lds_barrier();
             if (w >= np && d < 2) {
             } else if (d == 0) {
 #pragma unroll

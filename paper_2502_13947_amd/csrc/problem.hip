@@ -491,35 +491,53 @@ extern "C" qb_status qb_init_solutions(int32_t n, int32_t z, uint64_t seed, uint
 }
 
 // ------------------------------------------------------------------ field H = X Q
-// Block: 256 columns i x 8 solutions; X chunk staged through LDS.
+// Block: 256 columns i x 8 solutions x a range of rows; X staged through LDS,
+// the 8 solutions' bits of a row in one 8-byte word.  What bounds it: the
+// chain of row loads, so the rows are split over blockIdx.z until the card is
+// full (H is zeroed before and the partial sums are added with integer
+// atomics: exact, any order) and 16 loads are in flight at once (n = 2500, 4
+// solutions: 405 us unsplit with one load in flight, 23 us so).
+constexpr int FD_ROWS = 64;
+
 __global__ void __launch_bounds__(256) k_field(const int16_t *__restrict__ Q, int n, int z,
-                                               const uint8_t *__restrict__ X, int32_t *__restrict__ H)
+                                               const uint8_t *__restrict__ X, int32_t *__restrict__ H, int rows)
 {
-    constexpr int ZT = 8, JC = 256;
-    __shared__ uint8_t xs[ZT][JC];
+    constexpr int ZT = 8;
+    __shared__ __align__(8) uint8_t xs[FD_ROWS][ZT];
     const int i = blockIdx.x * 256 + threadIdx.x;
     const int p0 = blockIdx.y * ZT;
+    const int jb = blockIdx.z * rows, je = min(jb + rows, n);
     int32_t acc[ZT] = {0};
-    for (int j0 = 0; j0 < n; j0 += JC) {
+    for (int j0 = jb; j0 < je; j0 += FD_ROWS) {
         __syncthreads();
-        for (int t = threadIdx.x; t < ZT * JC; t += 256) {
-            const int pp = t / JC, jj = t % JC;
-            xs[pp][jj] = (p0 + pp < z && j0 + jj < n) ? X[(int64_t)(p0 + pp) * n + j0 + jj] : 0;
+#pragma unroll
+        for (int t = threadIdx.x; t < ZT * FD_ROWS; t += 256) {
+            const int pp = t / FD_ROWS, jj = t % FD_ROWS;
+            xs[jj][pp] = (p0 + pp < z && j0 + jj < je) ? X[(int64_t)(p0 + pp) * n + j0 + jj] : 0;
         }
         __syncthreads();
         if (i < n) {
-            const int jn = min(JC, n - j0);
+            const int jn = min(FD_ROWS, je - j0);
+#pragma unroll 16
             for (int jj = 0; jj < jn; ++jj) {
                 const int32_t q = Q[(int64_t)(j0 + jj) * n + i];
+                const uint2 x = *reinterpret_cast<const uint2 *>(xs[jj]);
 #pragma unroll
-                for (int pp = 0; pp < ZT; ++pp) acc[pp] += q * xs[pp][jj];
+                for (int pp = 0; pp < 4; ++pp) {
+                    acc[pp] += q * (int32_t)((x.x >> (8 * pp)) & 255u);
+                    acc[4 + pp] += q * (int32_t)((x.y >> (8 * pp)) & 255u);
+                }
             }
         }
     }
     if (i < n)
 #pragma unroll
         for (int pp = 0; pp < ZT; ++pp)
-            if (p0 + pp < z) H[(int64_t)(p0 + pp) * n + i] = acc[pp];
+            if (p0 + pp < z) {
+                int32_t *h = &H[(int64_t)(p0 + pp) * n + i];
+                if (gridDim.z == 1) *h = acc[pp];
+                else if (acc[pp]) atomicAdd(h, acc[pp]);
+            }
 }
 
 qb_status qb_rankk_mfma_launch(qb_problem P, int z, const int8_t *dX, int32_t *H, hipStream_t s);
@@ -535,34 +553,62 @@ extern "C" qb_status qb_field(qb_problem P, int32_t z, const uint8_t *X_d, int32
         if (rc != QB_OK) return rc;
         return qb_rankk_mfma_launch(P, z, (const int8_t *)X_d, H_d, qb_stream(stream));
     }
-    dim3 grid((P->n + 255) / 256, (z + 7) / 8);
-    k_field<<<grid, 256, 0, qb_stream(stream)>>>(P->Q, P->n, z, X_d, H_d);
+    const int gx = (P->n + 255) / 256, gy = (z + 7) / 8;
+    // rows per workgroup: a multiple of 64, so that about 1024 workgroups share the work
+    const int64_t want = 1024 / ((int64_t)gx * gy) > 1 ? 1024 / ((int64_t)gx * gy) : 1;
+    const int rows = FD_ROWS * (int)((P->n + FD_ROWS * want - 1) / (FD_ROWS * want));
+    dim3 grid(gx, gy, (P->n + rows - 1) / rows);
+    if (grid.z > 1) {
+        qb_status rc = qb_zero(H_d, sizeof(int32_t) * (size_t)z * P->n, stream);
+        if (rc != QB_OK) return rc;
+    }
+    k_field<<<grid, 256, 0, qb_stream(stream)>>>(P->Q, P->n, z, X_d, H_d, rows);
     QB_LAUNCH_CHECK();
     return QB_OK;
 }
 
 // ------------------------------------------------------------------ energy
-__global__ void __launch_bounds__(256) k_energy(int n, const uint8_t *__restrict__ X,
-                                                const int32_t *__restrict__ H, int64_t *__restrict__ E)
+// One workgroup of TB threads per solution, four variables per load.  What
+// bounds it: the round trips to memory, so rows longer than one load of 256
+// threads take 1024 (n = 7000, 256 solutions: 17 us with 256 threads and byte
+// loads, 4.5 us so).
+template <int TB>
+__global__ void __launch_bounds__(TB) k_energy(int n, const uint8_t *__restrict__ X,
+                                               const int32_t *__restrict__ H, int64_t *__restrict__ E)
 {
-    __shared__ int64_t part[4];
+    __shared__ int64_t part[TB / 64];
     const int p = blockIdx.x;
     const uint8_t *x = X + (int64_t)p * n;
     const int32_t *h = H + (int64_t)p * n;
     int64_t acc = 0;
-    for (int i = threadIdx.x; i < n; i += 256)
-        if (x[i]) acc += h[i];
+    const int n4 = n & ~3;
+#pragma unroll 2
+    for (int i = 4 * threadIdx.x; i < n4; i += 4 * TB) {
+        uint8_t b[4];
+        int32_t v[4];
+        __builtin_memcpy(b, x + i, sizeof b);        // rows start at any byte
+        __builtin_memcpy(v, h + i, sizeof v);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc += b[c] ? v[c] : 0;
+    }
+    if ((int)threadIdx.x < n - n4 && x[n4 + threadIdx.x]) acc += h[n4 + threadIdx.x];
     acc = qb_wave_sum_i64(acc);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) E[p] = part[0] + part[1] + part[2] + part[3];
+    if (threadIdx.x == 0) {
+        int64_t e = 0;
+#pragma unroll
+        for (int w = 0; w < TB / 64; ++w) e += part[w];
+        E[p] = e;
+    }
 }
 
 extern "C" qb_status qb_energy(int32_t n, int32_t z, const uint8_t *X_d, const int32_t *H_d,
                               int64_t *E_d, void *stream)
 {
     if (n < 1 || z < 1 || !X_d || !H_d || !E_d) return QB_E_ARG;
-    k_energy<<<z, 256, 0, qb_stream(stream)>>>(n, X_d, H_d, E_d);
+    if (n <= 1024) k_energy<256><<<z, 256, 0, qb_stream(stream)>>>(n, X_d, H_d, E_d);
+    else k_energy<1024><<<z, 1024, 0, qb_stream(stream)>>>(n, X_d, H_d, E_d);
     QB_LAUNCH_CHECK();
     return QB_OK;
 }

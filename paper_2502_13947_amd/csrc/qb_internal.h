@@ -321,6 +321,14 @@ __device__ __forceinline__ void qb_accept_sign(uint64_t ym, int k, int32_t p, in
     }
 }
 
+// A barrier that orders LDS only: loads from memory stay in flight over it.
+__device__ __forceinline__ void qb_lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 __device__ __forceinline__ int64_t qb_wave_sum_i64(int64_t v)
 {
 #pragma unroll

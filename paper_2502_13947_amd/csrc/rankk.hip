@@ -1,155 +1,223 @@
 // Rank-k local-field update H[p] += Q dX[p] (the Tabu section's O(n)
 // move-value update generalised to every variable a stage changed).
 //
-// VALU variant (any Q, best for few solutions or few changed variables): per (solution, column slice) the changed variables of dX[p]
-// are compacted into an LDS list, then every thread adds +-Q[j][i] for its
-// columns i (Q is symmetric, so column j of Q is row j: coalesced reads).
+// VALU variant (any Q, best for few solutions): a workgroup has 1024 columns
+// of one solution and a range of rows; the changed variables of the range are
+// compacted into an LDS list and every thread adds +-Q[j][i] for its four
+// consecutive columns (Q is symmetric, so column j of Q is row j).
 #include "qb_internal.h"
 
 namespace {
 
-constexpr int RK_CHUNK = 4096;
+// What bounds it: the chain of row loads, so the rows are split over
+// blockIdx.z until the card is full (partial sums added with integer atomics:
+// exact, any order) and eight of a thread's loads are in flight at once.
+// RK_ROWS of the range are compacted at a time
+// (n = 2500, 4 solutions: 68 us unsplit with one load in flight, 5.3 us so).
+constexpr int RK_ROWS = 256;
 
-template <typename QT, int CPT>
+template <typename QT>
 __global__ void __launch_bounds__(256) k_rankk_valu(const QT *__restrict__ Q, int n, const int8_t *__restrict__ dX,
-                                                    int32_t *__restrict__ H)
+                                                    int32_t *__restrict__ H, int rows)
 {
-    __shared__ int32_t list[RK_CHUNK];
-    __shared__ int cnt;
-    const int p = blockIdx.y, tid = threadIdx.x;
-    const int i0 = blockIdx.x * 256 * CPT;
+    __shared__ int32_t list[RK_ROWS + 7];            // padded to a multiple of 8 with 0 = no row
+    __shared__ int wcnt[4];
+    const int p = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i = blockIdx.x * 1024 + 4 * tid;
     const int8_t *d = dX + (int64_t)p * n;
-    int32_t acc[CPT];
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) acc[c] = 0;
-    for (int j0 = 0; j0 < n; j0 += RK_CHUNK) {
-        if (tid == 0) cnt = 0;
+    const int jb = blockIdx.z * rows, je = min(jb + rows, n);
+    int32_t acc[4] = {0, 0, 0, 0};
+    for (int j0 = jb; j0 < je; j0 += RK_ROWS) {
+        const int j = j0 + tid;
+        const int v = j < je ? d[j] : 0;
+        const uint64_t mask = __ballot(v != 0);
+        if (lane == 0) wcnt[wave] = __popcll(mask);
         __syncthreads();
-        for (int t = tid; t < RK_CHUNK; t += 256) {
-            const int j = j0 + t;
-            if (j < n) {
-                const int v = d[j];
-                if (v) list[atomicAdd(&cnt, 1)] = v > 0 ? (j + 1) : -(j + 1);
-            }
+        int base = 0, cnt = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            base += w < wave ? wcnt[w] : 0;
+            cnt += wcnt[w];
         }
+        if (v) list[base + __popcll(mask & ((1ull << lane) - 1))] = v > 0 ? (j + 1) : -(j + 1);
+        if (tid < 7) list[cnt + tid] = 0;
         __syncthreads();
-        const int c_n = cnt;
-        for (int u = 0; u < c_n; ++u) {
-            const int32_t v = list[u];
-            const int32_t s = v < 0 ? -1 : 1;
-            const QT *row = Q + (int64_t)(v < 0 ? -v - 1 : v - 1) * n;
+        if (i + 4 <= n) {
+            for (int u = 0; u < cnt; u += 8) {
+                QT q[8][4];                          // one load each, at any alignment
+                int32_t sg[8];
 #pragma unroll
-            for (int c = 0; c < CPT; ++c) {
-                const int i = i0 + tid + 256 * c;
-                if (i < n) acc[c] += s * (int32_t)row[i];
+                for (int v = 0; v < 8; ++v) {
+                    const int32_t e = __builtin_amdgcn_readfirstlane(list[u + v]);
+                    sg[v] = e > 0 ? 1 : e < 0 ? -1 : 0;
+                    __builtin_memcpy(q[v], Q + (int64_t)(e > 0 ? e - 1 : e < 0 ? -e - 1 : 0) * n + i, sizeof q[v]);
+                }
+#pragma unroll
+                for (int v = 0; v < 8; ++v)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[c] += sg[v] * (int32_t)q[v][c];
+            }
+        } else if (i < n) {                          // the last, partial group of columns
+            for (int u = 0; u < cnt; ++u) {
+                const int32_t e = list[u];
+                const int32_t sg = e < 0 ? -1 : 1;
+                const QT *row = Q + (int64_t)(e < 0 ? -e - 1 : e - 1) * n;
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (i + c < n) acc[c] += sg * (int32_t)row[i + c];
             }
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) {
-        const int i = i0 + tid + 256 * c;
-        if (i < n && acc[c]) H[(int64_t)p * n + i] += acc[c];
-    }
+    for (int c = 0; c < 4; ++c)
+        if (acc[c]) {                                // never past n: those sums stay 0
+            int32_t *h = &H[(int64_t)p * n + i + c];
+            if (gridDim.z == 1) *h += acc[c];
+            else atomicAdd(h, acc[c]);
+        }
 }
 
 // ------------------------------------------------------------------ MFMA variant
 // H (z x n) += dX (z x n, int8) . Q (n x n, int8): a real dense contraction.
 // Q is symmetric, so the B operand's column i is row i of the padded copy Qp
 // (K-contiguous, like the A operand's rows of dX).  v_mfma_i32_16x16x64_i8
-// with int32 accumulation is exact (|sum| <= n * 127 * 1).  Workgroup tile:
-// 64 solutions x 128 columns, four waves of 32 x 64 (2 x 4 MFMA tiles);
-// K is split across blockIdx.z and the partial sums are added with integer
-// atomics (exact and order independent).
+// with int32 accumulation is exact (|sum| <= n * 127 * 1).
+//
+// What bounds it: reading Q once (n*n bytes) and feeding the matrix cores.  A
+// workgroup has 64*WM solutions (all of up to 256, so that Q is read once) x
+// 128 columns, a wave 64 x 64 of them.  Steps of 128 rows go from memory to
+// registers two steps ahead and through two LDS buffers, so that every row is
+// read once per workgroup in whole 128-byte lines; rows of 144 bytes in LDS
+// give the 16-byte operand reads of 16 lanes distinct banks.  K is split over
+// blockIdx.z and the partial sums are added with integer atomics (exact and
+// order independent).  n = 7000, 256 solutions: 74 us with 64 solutions per
+// workgroup and operands straight from memory, 33 us so.
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-template <int AW>
+constexpr int RM_K = 128, RM_N = 128, RM_LD = RM_K + 16;
+
+// 16 bytes of a row of dX (rows start at any byte: one load at any alignment)
 __device__ __forceinline__ v4i load_a16(const int8_t *__restrict__ row, int kk, int n)
 {
     v4i v = {0, 0, 0, 0};
     if (kk + 16 <= n) {
-        if constexpr (AW == 16) {
-            v = *reinterpret_cast<const v4i *>(row + kk);
-        } else if constexpr (AW == 8) {
-            const int2 lo = *reinterpret_cast<const int2 *>(row + kk);
-            const int2 hi = *reinterpret_cast<const int2 *>(row + kk + 8);
-            v = v4i{lo.x, lo.y, hi.x, hi.y};
-        } else if constexpr (AW == 4) {
-            const int *w = reinterpret_cast<const int *>(row + kk);
-            v = v4i{w[0], w[1], w[2], w[3]};
-        } else {
-            uint32_t w[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int b = 0; b < 16; ++b) w[b >> 2] |= (uint32_t)(uint8_t)row[kk + b] << (8 * (b & 3));
-            v = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-        }
+        __builtin_memcpy(&v, row + kk, 16);
     } else if (kk < n) {
         uint32_t w[4] = {0, 0, 0, 0};
-        for (int b = 0; b < 16 && kk + b < n; ++b) w[b >> 2] |= (uint32_t)(uint8_t)row[kk + b] << (8 * (b & 3));
+#pragma unroll
+        for (int b = 0; b < 16; ++b)
+            if (kk + b < n) w[b >> 2] |= (uint32_t)(uint8_t)row[kk + b] << (8 * (b & 3));
         v = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
     }
     return v;
 }
 
-template <int AW>
-__global__ void __launch_bounds__(256) k_rankk_mfma(const int8_t *__restrict__ dX, int n, int z,
-                                                    const int8_t *__restrict__ Qp, int ldp, int32_t *__restrict__ H,
-                                                    int kchunk)
+template <int WM>
+__global__ void __launch_bounds__(128 * WM) k_rankk_mfma(const int8_t *__restrict__ dX, int n, int z,
+                                                         const int8_t *__restrict__ Qp, int ldp,
+                                                         int32_t *__restrict__ H, int kchunk)
 {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int m0 = blockIdx.y * 64 + (wave >> 1) * 32;
-    const int n0 = blockIdx.x * 128 + (wave & 1) * 64;
-    const int kend_all = (n + 63) & ~63;
+    constexpr int TB = 128 * WM, RPT = TB / 8;       // rows loaded by one round of the workgroup
+    constexpr int NA = 64 * WM / RPT, NB = RM_N / RPT;
+    __shared__ __align__(16) int8_t la[2][64 * WM][RM_LD];
+    __shared__ __align__(16) int8_t lb[2][RM_N][RM_LD];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int m0 = blockIdx.y * (64 * WM), n0 = blockIdx.x * RM_N;
+    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+    const int kpad = (n + 63) & ~63;                 // Qp is zero from n to here
     const int kbeg = blockIdx.z * kchunk;
-    const int kend = min(kbeg + kchunk, kend_all);
+    const int nstep = (min(kchunk, kpad - kbeg) + RM_K - 1) / RM_K;
     const int r16 = lane & 15, g = lane >> 4;
-    v4i acc[2][4];
+    const int lrow = tid >> 3, lcol = (tid & 7) * 16;
+    struct Stage { v4i a[NA], b[NB]; };
+    auto fetch = [&](Stage &st, int step) {
+        const int kk = kbeg + step * RM_K + lcol;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+        for (int i = 0; i < NA; ++i) {
+            const int p = m0 + lrow + i * RPT;
+            st.a[i] = step < nstep && p < z ? load_a16(dX + (int64_t)p * n, kk, n) : v4i{0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int c = n0 + lrow + i * RPT;
+            st.b[i] = step < nstep && c < n && kk < kpad
+                          ? *reinterpret_cast<const v4i *>(Qp + (int64_t)c * ldp + kk) : v4i{0, 0, 0, 0};
+        }
+    };
+    auto stash = [&](const Stage &st, int buf) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) *reinterpret_cast<v4i *>(&la[buf][lrow + i * RPT][lcol]) = st.a[i];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) *reinterpret_cast<v4i *>(&lb[buf][lrow + i * RPT][lcol]) = st.b[i];
+    };
+    v4i acc[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = v4i{0, 0, 0, 0};
-    const int8_t *arow[2];
-    bool aok[2];
+    auto multiply = [&](int buf) {
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi) {
-        const int p = m0 + mi * 16 + r16;
-        aok[mi] = p < z;
-        arow[mi] = dX + (int64_t)(aok[mi] ? p : 0) * n;
-    }
-    const int8_t *brow[4];
-    bool bok[4];
+        for (int k = 0; k < RM_K; k += 64) {
+            v4i a[4], b[4];
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni) {
-        const int i = n0 + ni * 16 + r16;
-        bok[ni] = i < n;
-        brow[ni] = Qp + (int64_t)(bok[ni] ? i : 0) * ldp;
-    }
-    for (int k0 = kbeg; k0 < kend; k0 += 64) {
-        const int kk = k0 + g * 16;
-        v4i a[2], b[4];
+            for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const v4i *>(&la[buf][wm + 16 * i + r16][k + 16 * g]);
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi) a[mi] = aok[mi] ? load_a16<AW>(arow[mi], kk, n) : v4i{0, 0, 0, 0};
+            for (int i = 0; i < 4; ++i) b[i] = *reinterpret_cast<const v4i *>(&lb[buf][wn + 16 * i + r16][k + 16 * g]);
 #pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
-            b[ni] = bok[ni] ? *reinterpret_cast<const v4i *>(brow[ni] + kk) : v4i{0, 0, 0, 0};
+            for (int mi = 0; mi < 4; ++mi)
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < 4; ++ni)
-                acc[mi][ni] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
+                for (int ni = 0; ni < 4; ++ni)
+                    acc[mi][ni] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
+        }
+    };
+    // step s is multiplied from buffer s & 1 while step s + 1 is in registers
+    // or on its way and step s + 2 is asked for
+    Stage s0, s1;
+    fetch(s0, 0);
+    fetch(s1, 1);
+    stash(s0, 0);
+    for (int step = 0; step < nstep; step += 2) {
+        fetch(s0, step + 2);
+        qb_lds_barrier();
+        multiply(0);
+        stash(s1, 1);
+        fetch(s1, step + 3);
+        qb_lds_barrier();
+        multiply(1);                                 // zeros past the last step
+        stash(s0, 0);
     }
     // 16x16 result layout: lane holds rows 4g..4g+3 of column r16
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
+    for (int mi = 0; mi < 4; ++mi)
 #pragma unroll
         for (int ni = 0; ni < 4; ++ni)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int p = m0 + mi * 16 + 4 * g + r;
-                const int i = n0 + ni * 16 + r16;
+                const int p = m0 + wm + mi * 16 + 4 * g + r;
+                const int i = n0 + wn + ni * 16 + r16;
                 const int32_t v = acc[mi][ni][r];
                 if (p < z && i < n && v != 0) atomicAdd(&H[(int64_t)p * n + i], v);
             }
+}
+
+template <int WM>
+qb_status rankk_mfma_go(qb_problem P, int z, const int8_t *dX, int32_t *H, hipStream_t s)
+{
+    const int n = P->n;
+    const int gx = (n + RM_N - 1) / RM_N, gy = (z + 64 * WM - 1) / (64 * WM);
+    const int nk = (n + RM_K - 1) / RM_K;
+    // LDS holds one workgroup of WM = 4 on a compute unit, two of the others
+    int ncu = 0;
+    QB_TRY_HIP(qb_cu_count(&ncu));
+    const int fit = ncu * (WM == 4 ? 1 : 2);
+    int split = fit / (gx * gy);
+    split = split < 1 ? 1 : split > nk ? nk : split;
+    const int steps = (nk + split - 1) / split;
+    k_rankk_mfma<WM><<<dim3(gx, gy, (nk + steps - 1) / steps), 128 * WM, 0, s>>>(
+        dX, n, z, (const int8_t *)P->Qp, P->ldp, H, RM_K * steps);
+    QB_LAUNCH_CHECK();
+    return QB_OK;
 }
 
 // Sparse product over the row-major ELL: H[p][i] (+)= Q_ii V[p][i] +
@@ -191,25 +259,8 @@ qb_status qb_field_ell_launch(qb_problem P, int z, const uint8_t *X, int32_t *H,
 
 qb_status qb_rankk_mfma_launch(qb_problem P, int z, const int8_t *dX, int32_t *H, hipStream_t s)
 {
-    const int n = P->n;
-    const int gx = (n + 127) / 128, gy = (z + 63) / 64;
-    const int nk = (n + 63) / 64;
-    int split = (512 + gx * gy - 1) / (gx * gy);
-    split = split < 1 ? 1 : split > nk ? nk : split;
-    const int kchunk = 64 * ((nk + split - 1) / split);
-    split = (nk * 64 + kchunk - 1) / kchunk;
-    dim3 grid(gx, gy, split);
-    const int8_t *Qp = (const int8_t *)P->Qp;
-    if (n % 16 == 0)
-        k_rankk_mfma<16><<<grid, 256, 0, s>>>(dX, n, z, Qp, P->ldp, H, kchunk);
-    else if (n % 8 == 0)
-        k_rankk_mfma<8><<<grid, 256, 0, s>>>(dX, n, z, Qp, P->ldp, H, kchunk);
-    else if (n % 4 == 0)
-        k_rankk_mfma<4><<<grid, 256, 0, s>>>(dX, n, z, Qp, P->ldp, H, kchunk);
-    else
-        k_rankk_mfma<1><<<grid, 256, 0, s>>>(dX, n, z, Qp, P->ldp, H, kchunk);
-    QB_LAUNCH_CHECK();
-    return QB_OK;
+    return z <= 64 ? rankk_mfma_go<1>(P, z, dX, H, s)
+           : z <= 128 ? rankk_mfma_go<2>(P, z, dX, H, s) : rankk_mfma_go<4>(P, z, dX, H, s);
 }
 
 extern "C" qb_status qb_rankk(qb_problem P, int32_t z, const int8_t *dX_d, int32_t *H_d, int32_t variant,
@@ -225,17 +276,20 @@ extern "C" qb_status qb_rankk(qb_problem P, int32_t z, const int8_t *dX_d, int32
         return QB_OK;
     }
     if (variant == 3 || (variant == 2 && !P->int8_ok)) return QB_E_UNSUPPORTED;
-    constexpr int CPT = 4;
-    dim3 grid((P->n + 256 * CPT - 1) / (256 * CPT), z);
     if (variant == 0) variant = (P->int8_ok && P->Qp && z >= 32) ? 2 : 1;
     if (variant == 2) {
         if (!P->Qp) return QB_E_UNSUPPORTED;
         return qb_rankk_mfma_launch(P, z, dX_d, H_d, s);
     }
+    const int gx = (P->n + 1023) / 1024;
+    // rows per workgroup: a multiple of 64, so that about 1024 workgroups share the work
+    const int64_t want = 1024 / ((int64_t)gx * z) > 1 ? 1024 / ((int64_t)gx * z) : 1;
+    const int rows = 64 * (int)((P->n + 64 * want - 1) / (64 * want));
+    dim3 grid(gx, z, (P->n + rows - 1) / rows);
     if (P->int8_ok)
-        k_rankk_valu<int8_t, CPT><<<grid, 256, 0, s>>>(P->Q8, P->n, dX_d, H_d);
+        k_rankk_valu<int8_t><<<grid, 256, 0, s>>>(P->Q8, P->n, dX_d, H_d, rows);
     else
-        k_rankk_valu<int16_t, CPT><<<grid, 256, 0, s>>>(P->Q, P->n, dX_d, H_d);
+        k_rankk_valu<int16_t><<<grid, 256, 0, s>>>(P->Q, P->n, dX_d, H_d, rows);
     QB_LAUNCH_CHECK();
     return QB_OK;
 }
