@@ -89,8 +89,8 @@ __global__ void k_pad_copy(const int16_t *__restrict__ Q, int n, int ld, T *__re
         out[(int64_t)i * ld + j] = j < n ? (T)Q[(int64_t)i * n + j] : (T)0;
 }
 
-// Rows of Q in the dense Tabu kernel's thread order (qb_tabu_pos), zero
-// past column n.
+// Rows of Q in the dense Tabu kernel's thread order (qb_tabu_pos), zero on
+// the diagonal (the kernel keeps Q_jj in the move values) and past column n.
 template <typename T>
 __global__ void k_tabu_copy(const int16_t *__restrict__ Q, int n, int ld, int ept, int tb, T *__restrict__ out)
 {
@@ -98,7 +98,7 @@ __global__ void k_tabu_copy(const int16_t *__restrict__ Q, int n, int ld, int ep
     // the ept * tb elements of a row; a slot's padding is left as it is
     for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < ept * tb; j += gridDim.x * blockDim.x) {
         const int pos = qb_tabu_pos(j / tb, j % tb, ept, (int)sizeof(T), tb);
-        out[(int64_t)i * ld + pos] = j < n ? (T)Q[(int64_t)i * n + j] : (T)0;
+        out[(int64_t)i * ld + pos] = j < n && j != i ? (T)Q[(int64_t)i * n + j] : (T)0;
     }
 }
 

@@ -47,16 +47,17 @@ static inline __host__ __device__ uint32_t qb_ell_word(int32_t v, int col)
 static inline __host__ __device__ int qb_ell_col(uint32_t w) { return (int)(w & 0xffffu); }
 static inline __host__ __device__ int32_t qb_ell_val(uint32_t w) { return (int32_t)w >> 16; }
 
-// Threads of the dense Tabu workgroup for n variables: 1024 (sixteen waves),
-// or 512 where that measured faster on MI355X.  With 1024 threads, n in
-// (2048, 3072] or (4096, 5120] gives each thread 3 or 5 variables, which it
-// reads in two chunks; eight waves with 5, 6 or 10 variables each then do
-// the step 5-6 % faster (at n = 2500 and 5000), while elsewhere sixteen
-// waves are as fast or faster (n = 1000, 4000, 6000, 7000, 8000 measured).
+// Threads of the dense Tabu workgroup for n variables.  A step is a serial
+// chain that every wave walks, so few waves with many variables each win: at
+// n = 1000 one, four and eight waves take 0.51, 0.55 and 0.61 us per step, at
+// n = 1500 0.54, 0.57 and 0.62, at n = 2000 0.60, 0.58 and 0.63, and at n =
+// 7000 four, eight and sixteen waves 0.75, 0.74 and 0.88 (int8).  Thirty-two
+// variables per thread are the most the kernel keeps in registers.
+// QB_TABU_THREADS is the width for move values too large for the others' keys.
 #define QB_TABU_THREADS 1024
 static inline __host__ __device__ int qb_tabu_threads(int n)
 {
-    return ((n > 2048 && n <= 3072) || (n > 4096 && n <= 5120)) ? 512 : QB_TABU_THREADS;
+    return n <= 1536 ? 64 : n <= 8192 ? 256 : 512;
 }
 
 // Elements per thread of the dense Tabu kernel with tb threads (the padded
@@ -64,9 +65,14 @@ static inline __host__ __device__ int qb_tabu_threads(int n)
 // too large.
 static inline int qb_tabu_ept(int n, int tb)
 {
-    // beyond 16 elements per thread the state no longer fits 128 VGPRs
-    static const int opts[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16};
-    for (int e : opts)
+    static const int wide[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16};
+    static const int deep[] = {1, 2, 4, 8, 12, 16, 20, 24, 28, 32};
+    if (tb == QB_TABU_THREADS) {
+        for (int e : wide)
+            if (n <= tb * e) return e;
+        return 0;
+    }
+    for (int e : deep)
         if (n <= tb * e) return e;
     return 0;
 }

@@ -1,33 +1,37 @@
 // Tabu search (Alg. 1 of the IC-D^2S paper) on gfx950: one workgroup per
-// solution, of 1024 threads (sixteen waves, four per SIMD, so the per-step
-// element work is spread thin and one wave's latency overlaps the others'
-// work), or of 512 threads at the sizes where eight waves measured faster
-// (qb_tabu_threads).
+// solution, of one wave up to 1536 variables, four up to 8192 and eight
+// beyond (qb_tabu_threads).
 //
 // Thread t owns the variables j = e*TB + t (e < EPT) and keeps in
-// registers, per variable: the move value D_j = Q_jj + 2(1-2x_j)h_j (biased
-// to be non-negative), the factor S_j = 2(1-2x_j), and the step U_j after
-// which the variable is free again.  U replaces the tenure vector of the
-// listing: "C_j <= 0 at step t" is exactly "U_j <= t-1" when U is updated
-// only for the flipped variable, so no per-step decrement pass is needed.
+// registers, per variable: a key of the move value D_j = Q_jj + 2(1-2x_j)h_j
+// (biased to be non-negative), the element e and, in the top bit, whether the
+// variable is tabu; and the factor S_j = 2(1-2x_j).
 //
-// One step: every lane forms a 32-bit key (move value, element) for each of
-// its allowed variables (not tabu, or aspirating: OV + D < OV_min) and keeps
-// the minimum; the wave minimum comes from DPP row operations and the row
-// broadcasts; index order inside a wave is (element, lane), so the lowest
-// lane holding the minimal key gives the lowest index; the sixteen wave
-// winners meet in LDS (one barrier per step, double-buffered slots, the
-// step loop run in pairs so every slot address is fixed), where a DPP
+// One step: every lane takes the minimum of its allowed keys (not tabu, or
+// aspirating: OV + D < OV_min); the wave minimum comes from DPP row
+// operations and the row broadcasts; index order inside a wave is (element,
+// lane), so the lowest lane holding the minimal key gives the lowest index;
+// the wave winners meet in LDS (one barrier per step, double-buffered slots,
+// the step loop run in pairs so every slot address is fixed), where a DPP
 // minimum over lanes picks the smallest (32-bit (key, wave) when the move
 // values allow, else 64-bit (move, index, x)).  The chosen variable's row is
 // read from the Tabu copy of Q, where each thread's elements lie in one
 // padded, naturally aligned slot of up to 16 bytes, or in a few aligned
-// chunks beyond that (qb_tabu_pos), so a wave issues one vector load per
-// slot or chunk rather than one byte load per element; every D is updated by
-// one multiply-add and the owner of the flipped variable patches its own
-// element.  x_min is never copied: per-variable "flipped since the last
-// improvement" bits recover it, and the field is moved to x_min with the
-// rows of the differing variables.
+// chunks beyond that (qb_tabu_pos); each element's update is one dot product
+// of its row word with S_j at the element's place of the word.  x_min is
+// never copied: per-variable "flipped since the last improvement" bits
+// recover it, and the field is moved to x_min with the rows of the differing
+// variables.
+//
+// What bounds it: the instructions of one step's chain, which every wave
+// walks (without the row loads a step takes as long, so memory is hidden).
+// Hence few waves, no per-element work but a dot product and two minima, and
+// everything that is not on the way from a row to the next winner -- the
+// owner's patch, the tabu lists, the books -- placed while the row is on its
+// way.  One variable at most is released per step without any scan: the ring
+// of flips names it.  Against sixteen waves that scanned their own release
+// steps and patched after the row: n = 7000, 256 solutions 1.01 -> 0.75 us
+// per step, n = 2500 0.75 -> 0.60, n = 1000 0.63 -> 0.51, n = 256 0.60 -> 0.45.
 #include <algorithm>
 
 #include "qb_internal.h"
@@ -48,68 +52,95 @@ template <int TB>
 struct TabuShape {
     static constexpr int NW = TB / 64;
     static constexpr int WB = qb_ceil_log2(NW);
-    static_assert(TB == 512 || TB == 1024, "eight or sixteen waves");
+    static_assert(NW <= 16 && (NW & (NW - 1)) == 0, "a power of two of waves");
 };
 
 constexpr int qb_pow2_at_least(int v) { return v <= 1 ? 1 : 2 * qb_pow2_at_least((v + 1) / 2); }
 
-// Thread tid's elements of one row of the Tabu copy of Q (the order of
-// qb_tabu_pos), sign-extended: up to 16 bytes one naturally aligned load of
-// the thread's padded slot; beyond, one load per chunk, chunks of SZ
-// elements from element START on.
-template <typename QT, int EPT, int TB, int START = 0, int SZ = 16 / (int)sizeof(QT)>
-__device__ __forceinline__ void tabu_row(const QT *row, uint32_t tid, int32_t (&q)[EPT])
-{
-    constexpr int BYTES_ALL = EPT * (int)sizeof(QT);
-    if constexpr (START == 0 && BYTES_ALL <= 16 && qb_pow2_at_least(BYTES_ALL) != BYTES_ALL) {
-        constexpr int SLOT = qb_pow2_at_least(BYTES_ALL);     // bytes
-        const uint8_t *p = reinterpret_cast<const uint8_t *>(row) + tid * (uint32_t)SLOT;
-        uint32_t w[4];
-        if constexpr (SLOT == 16) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(p);
-            w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
-        } else if constexpr (SLOT == 8) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(p);
-            w[0] = v.x; w[1] = v.y; w[2] = 0u; w[3] = 0u;
-        } else {
-            w[0] = *reinterpret_cast<const uint32_t *>(p); w[1] = w[2] = w[3] = 0u;
-        }
+// A thread's elements of one row of the Tabu copy of Q (the order of
+// qb_tabu_pos), as they lie in memory: element e in word e / EPW, at bit
+// BITS * (e % EPW).  Up to 16 bytes one naturally aligned load of the
+// thread's padded slot; beyond, one load per chunk.
+template <typename QT, int EPT, int TB>
+struct TabuRow {
+    static constexpr int ESZ = (int)sizeof(QT), EPW = 4 / ESZ, BITS = 8 * ESZ;
+    static constexpr int BYTES = EPT * ESZ;
+    static constexpr int SLOT = BYTES <= 16 ? qb_pow2_at_least(BYTES) : BYTES;
+    static_assert(SLOT <= 16 || SLOT % 4 == 0, "whole words");
+    static constexpr int NWD = (SLOT + 3) / 4;
+    uint32_t w[NWD];
+
+    // the chunk of SZ bytes at byte START of the thread's part, then the rest;
+    // the row's byte offset is a scalar, the thread's an unchanging register
+    template <int START = 0, int SZ = 16>
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rows, uint32_t row, uint32_t tid)
+    {
+        if constexpr (START < SLOT) {
+            if constexpr (SLOT - START >= SZ) {
+                const uint32_t at = START * TB + tid * (uint32_t)SZ;
+                if constexpr (SZ == 16) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rows, at, row, 0);
 #pragma unroll
-        for (int k = 0; k < EPT; ++k) {
-            const uint32_t word = w[(k * (int)sizeof(QT)) / 4];
-            const int sh = ((k * (int)sizeof(QT)) % 4) * 8;
-            q[k] = sizeof(QT) == 1 ? (int32_t)(int8_t)(word >> sh) : (int32_t)(int16_t)(word >> sh);
-        }
-    } else if constexpr (SZ >= 1 && START < EPT) {
-        if constexpr (EPT - START >= SZ) {
-            constexpr int BYTES = SZ * (int)sizeof(QT);
-            const uint8_t *p = reinterpret_cast<const uint8_t *>(row + START * TB) + tid * (uint32_t)BYTES;
-            uint32_t w[(BYTES + 3) / 4];
-            if constexpr (BYTES == 16) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(p);
-                w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
-            } else if constexpr (BYTES == 8) {
-                const uint2 v = *reinterpret_cast<const uint2 *>(p);
-                w[0] = v.x; w[1] = v.y;
-            } else if constexpr (BYTES == 4) {
-                w[0] = *reinterpret_cast<const uint32_t *>(p);
-            } else if constexpr (BYTES == 2) {
-                w[0] = *reinterpret_cast<const uint16_t *>(p);
+                    for (int k = 0; k < 4; ++k) w[START / 4 + k] = v[k];
+                } else if constexpr (SZ == 8) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rows, at, row, 0);
+                    w[START / 4] = v[0]; w[START / 4 + 1] = v[1];
+                } else if constexpr (SZ == 4) {
+                    w[START / 4] = __builtin_amdgcn_raw_buffer_load_b32(rows, at, row, 0);
+                } else if constexpr (SZ == 2) {
+                    w[START / 4] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rows, at, row, 0);
+                } else {
+                    w[START / 4] = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rows, at, row, 0);
+                }
+                load<START + SZ, SZ>(rows, row, tid);
             } else {
-                w[0] = *p;
+                load<START, SZ / 2>(rows, row, tid);
             }
-#pragma unroll
-            for (int k = 0; k < SZ; ++k) {
-                const uint32_t word = w[(k * (int)sizeof(QT)) / 4];
-                const int sh = ((k * (int)sizeof(QT)) % 4) * 8;
-                q[START + k] = sizeof(QT) == 1 ? (int32_t)(int8_t)(word >> sh) : (int32_t)(int16_t)(word >> sh);
-            }
-            tabu_row<QT, EPT, TB, START + SZ, SZ>(row, tid, q);
-        } else {
-            tabu_row<QT, EPT, TB, START, SZ / 2>(row, tid, q);
         }
     }
+
+    // a factor at element e's place of its word, and c + factor * element e:
+    // one dot product of the word with the factor's word (the other places 0)
+    static __device__ __forceinline__ uint32_t place(int e, int32_t f)
+    {
+        return ((uint32_t)f & (BITS == 8 ? 0xFFu : 0xFFFFu)) << (BITS * (e % EPW));
+    }
+    __device__ __forceinline__ uint32_t mad(int e, uint32_t factor, uint32_t c) const
+    {
+        if constexpr (ESZ == 1) {
+            return (uint32_t)__builtin_amdgcn_sdot4((int)w[e / EPW], (int)factor, (int)c, false);
+        } else {
+            typedef short v2s __attribute__((ext_vector_type(2)));
+            return (uint32_t)__builtin_amdgcn_sdot2(__builtin_bit_cast(v2s, w[e / EPW]),
+                                                    __builtin_bit_cast(v2s, factor), (int)c, false);
+        }
+    }
+};
+
+// The words of a row are not looked at before this point.
+template <int N>
+__device__ __forceinline__ void tabu_arrive(uint32_t (&w)[N])
+{
+#pragma unroll
+    for (int k = 0; k < N; ++k) asm volatile("" : "+v"(w[k]));
 }
+
+// A value computed in every lane (an update under a condition would copy the
+// whole vector around a branch).
+__device__ __forceinline__ uint32_t tabu_held(uint32_t v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// *p += 1 in LDS, nothing returned.
+__device__ __forceinline__ void lds_inc(int32_t *p)
+{
+    const uint32_t a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int32_t *)p;
+    asm volatile("ds_add_u32 %0, %1" ::"v"(a), "v"(1) : "memory");
+}
+
+constexpr int TABU_RING = 1024;   // flips remembered for the release of their variables
 
 template <int EPT, typename QT, bool K32, int TB>
 __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp, const int16_t *__restrict__ Q16,
@@ -123,7 +154,8 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
     constexpr uint32_t EMASK = (1u << EB) - 1u;
     __shared__ uint64_t red[2][NW];
     __shared__ uint64_t red2[NW];
-    __shared__ int32_t list[TB];
+    __shared__ int32_t list[TB + 3];             // padded to a multiple of 4 with 0 = no row
+    __shared__ int32_t hist[TABU_RING];
     __shared__ int lcount;
     extern __shared__ int32_t tl[];              // [0,n): flips, [n,2n): last-flip step
     int32_t *Ts = tl, *Ls = tl + n;
@@ -135,58 +167,62 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
     // padding elements carry the largest possible key, tabu for ever
     const uint32_t dpad = 0x7FFFFFFFu >> EB;
 
-    uint32_t Kb[EPT];      // ((D + bias) << EB | e) | TBIT if tabu
-    int32_t S[EPT];        // 2 (1 - 2 x) << EB
-    int32_t U[EPT];        // tabu through step U
-    uint32_t xb = 0;       // x bits of the owned variables (EPT <= 16)
+    using Row = TabuRow<QT, EPT, TB>;
+    const uint32_t pitch = (uint32_t)ldp * (uint32_t)sizeof(QT);
+    // n * pitch stays below 2^30 bytes; 0x27000: raw 32-bit elements
+    const __amdgpu_buffer_rsrc_t rows =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<QT *>(Qt), 0, (uint32_t)n * pitch, 0x27000);
+    // a row's product with S_j changes sign with the flip's direction: the
+    // bits in which +S and -S differ, at each place of a word
+    constexpr int32_t S0 = 2 << EB;
+    constexpr uint32_t SX = ((uint32_t)S0 ^ (uint32_t)-S0) & (Row::BITS == 8 ? 0xFFu : 0xFFFFu);
+    static_assert(S0 < 128, "S fits a byte");
+
+    // vectors, not arrays: a uniform index into sixteen or more elements moves
+    // one register (a select per element below that)
+    constexpr int KW = EPT <= 2 ? EPT : EPT <= 16 ? 16 : 32;
+    typedef uint32_t Keys __attribute__((ext_vector_type(KW)));
+    Keys Kb;               // ((D + bias) << EB | e) | TBIT if tabu
+    Keys S;                // turned * 2 (1 - 2 x) << EB, at the element's place of a row word
+    uint32_t xb = 0;       // x bits of the owned variables (EPT <= 32)
     uint32_t pb = 0;       // flipped since the last improvement
-    int32_t nexp = 0x7fffffff;   // smallest U among the thread's tabu variables
+    uint32_t late = 0;     // variables whose release the thread looks up itself
+    int32_t nexp = 0x7fffffff;   // the last tabu step of the first of those
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
         const int j = e * TB + tid;
-        U[e] = 0;
         if (j < n) {
             const int32_t x = X[ro + j] & 1;
             const int32_t qjj = Q16[(int64_t)j * n + j];
-            S[e] = (x ? -2 : 2) << EB;
+            S[e] = Row::place(e, x ? -S0 : S0);
             xb |= (uint32_t)x << e;
             Kb[e] = (((uint32_t)(qjj + (x ? -2 : 2) * H[ro + j]) + bias) << EB) | (uint32_t)e;
             Ts[j] = 0;
             Ls[j] = 0;
         } else {
-            S[e] = 2 << EB;
-            Kb[e] = (dpad << EB) | (uint32_t)e | TBIT;
-            U[e] = 0x7fffffff;                   // never allowed
+            S[e] = 0;
+            Kb[e] = (dpad << EB) | (uint32_t)e | TBIT;   // never released
         }
     }
-    int64_t OV = E[p];
+    int64_t OVmin = E[p];
     int64_t gap = 0;       // OV - OV_min, never negative
+    int32_t turned = 1;    // the direction of the last flip
     const int wu = __builtin_amdgcn_readfirstlane(wid);
+    // A variable flipped at step t is tabu through step t + tenure - 1, plus
+    // the tenure that was left when it aspirated.  Without such a rest the
+    // ring of flips names it when its time is over (-1: nobody).  With one, or
+    // with a tenure past the ring, it is `late`: its last tabu step waits in
+    // Tout (scratch until the end) and nexp.
+    const uint32_t far = tenure >= TABU_RING;
+    const uint32_t tnew = tenure >= 2 ? TBIT : 0u;
+    for (int t = tid; t < TABU_RING; t += TB) hist[t] = -1;
+    // aspiration: a tabu key k aspirates when (k >> EB) < OV_min - OV + bias,
+    // that is k < tbk (zero when nothing can aspirate)
+    uint32_t tbk = asp ? bias << EB : 0u;
 
     // One step; consecutive steps alternate the two slot buffers, so the loop
     // runs in pairs and every LDS address is fixed.
     auto one_step = [&](const int step, uint64_t *slots) {
-        // aspiration: a tabu key k aspirates when (k >> EB) < OV_min - OV + bias,
-        // that is k < tbk (zero when nothing can aspirate)
-        uint32_t tbk = 0;
-        {
-            const uint32_t gh = (uint32_t)((uint64_t)gap >> 32), gl = (uint32_t)gap;
-            if (asp && gh == 0u && gl < bias) tbk = (bias - gl) << EB;
-        }
-        const int32_t free_at = step - 1;
-        if (free_at >= nexp) {
-            // a tabu variable of this thread is free again.  Every variable
-            // that is not tabu has U <= free_at already (clearing its bit is a
-            // no-op), and padding never frees (U = INT_MAX), so no per-element
-            // branch is needed
-            nexp = 0x7fffffff;
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                const bool freed = U[e] <= free_at;
-                Kb[e] &= freed ? ~TBIT : ~0u;
-                nexp = min(nexp, freed ? 0x7fffffff : U[e]);
-            }
-        }
         // smallest free key (tabu keys carry bit 31, so they lose the
         // unsigned minimum) and smallest tabu key (they win the signed one);
         // the smallest tabu key aspirates whenever any does
@@ -201,130 +237,160 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
         const uint32_t tk = (uint32_t)m2 ^ TBIT;               // >= TBIT (never aspirates) when none is
         const uint32_t best = min(fk, tk < tbk ? tk : KNONE);
         const uint32_t wmin = qb_wave_min_u32_b(best);
+        // lowest index among the minimal moves of the wave: the lowest lane
+        // holding the minimal key (move, element)
+        auto lane_of = [&](uint32_t wm, uint32_t bsel) { return (int)__builtin_ctzll(__ballot(bsel == wm)); };
+        auto x_of = [&](uint32_t wm, int L) {
+            return ((uint32_t)__builtin_amdgcn_readlane((int)xb, L) >> (wm & EMASK)) & 1u;
+        };
         // the wave's winner slot for minimum key wm among the lanes' keys bsel
         // (a whole-wave call); padding keys never win a K32 slot
         auto slot_of = [&](uint32_t wm, uint32_t bsel) -> uint64_t {
-            // lowest index among the minimal moves: the lowest lane holding the
-            // minimal move value, then that lane's own lowest element
-            const uint64_t who = __ballot(bsel == wm);
-            const int L = __builtin_ctzll(who);
-            const int ew = (int)(wm & EMASK);
-            const uint32_t xw = ((uint32_t)__builtin_amdgcn_readlane((int)xb, L) >> ew) & 1u;
+            const int L = lane_of(wm, bsel);
+            const uint32_t xw = x_of(wm, L);
             if constexpr (K32) {
                 if (wm >= (1u << (31 - WB))) return ~0ull;
                 return ((uint64_t)(((uint32_t)L << 1) | xw) << 32) | ((wm << WB) | (uint32_t)wu);
             } else {
-                return qb_tabu_winner(wm >> EB, ew * TB + wu * 64 + L, xw);
+                return qb_tabu_winner(wm >> EB, (int)(wm & EMASK) * TB + wu * 64 + L, xw);
             }
         };
-        uint64_t wkey = ~0ull;
-        if (wmin != KNONE) wkey = slot_of(wmin, best);
-        if (lane == 0) slots[wid] = wkey;
-        __syncthreads();
         uint32_t dib;
-        int i;
+        int i, ei, ti;                             // the variable, its element and thread
         int32_t s;                                 // direction of x_i
-        if constexpr (K32) {
-            uint32_t key = 0, hi = 0;
-            if (!qb_pick32<NW>(slots, lane, key, hi)) {
+        if constexpr (NW == 1) {
+            __builtin_amdgcn_wave_barrier();
+            uint32_t wm = wmin, bsel = best;
+            if (__builtin_expect(wm == KNONE, 0)) {
                 // every variable is tabu and none aspirates: argmin over all of them
-                const uint32_t b2 = min(fk, tk);
-                const uint32_t w2 = qb_wave_min_u32_b(b2);
-                const uint64_t k2 = slot_of(w2, b2);
-                if (lane == 0) red2[wid] = k2;
-                __syncthreads();
-                qb_pick32<NW>(red2, lane, key, hi);
+                bsel = min(fk, tk);
+                wm = qb_wave_min_u32_b(bsel);
             }
-            const uint32_t wm = key >> WB;
+            ti = lane_of(wm, bsel);
+            s = x_of(wm, ti) ? -1 : 1;
             dib = wm >> EB;
-            i = (int)(wm & EMASK) * TB + (int)(key & (NW - 1)) * 64 + (int)(hi >> 1);
-            s = (hi & 1u) ? -1 : 1;
+            ei = (int)(wm & EMASK);
+            i = ei * TB + ti;
         } else {
-            uint64_t kb = qb_min_winners<NW>(slots, lane);
-            if (kb == ~0ull) {
-                // every variable is tabu and none aspirates: argmin over all of them
-                const uint32_t b2 = min(fk, tk);
-                const uint32_t w2 = qb_wave_min_u32_b(b2);
-                const uint64_t k2 = slot_of(w2, b2);
-                if (lane == 0) red2[wid] = k2;
-                __syncthreads();
-                kb = qb_min_winners<NW>(red2, lane);
+            uint64_t wkey = ~0ull;
+            if (wmin != KNONE) wkey = slot_of(wmin, best);
+            if (lane == 0) slots[wid] = wkey;
+            qb_lds_barrier();
+            if constexpr (K32) {
+                uint32_t key = 0, hi = 0;
+                if (__builtin_expect(!qb_pick32<NW>(slots, lane, key, hi), 0)) {
+                    // every variable is tabu and none aspirates: argmin over all of them
+                    const uint32_t b2 = min(fk, tk);
+                    const uint32_t w2 = qb_wave_min_u32_b(b2);
+                    const uint64_t k2 = slot_of(w2, b2);
+                    if (lane == 0) red2[wid] = k2;
+                    qb_lds_barrier();
+                    qb_pick32<NW>(red2, lane, key, hi);
+                }
+                const uint32_t wm = key >> WB;
+                dib = wm >> EB;
+                ei = (int)(wm & EMASK);
+                ti = (int)(key & (NW - 1)) * 64 + (int)(hi >> 1);
+                i = ei * TB + ti;
+                s = (hi & 1u) ? -1 : 1;
+            } else {
+                uint64_t kb = qb_min_winners<NW>(slots, lane);
+                if (__builtin_expect(kb == ~0ull, 0)) {
+                    // every variable is tabu and none aspirates: argmin over all of them
+                    const uint32_t b2 = min(fk, tk);
+                    const uint32_t w2 = qb_wave_min_u32_b(b2);
+                    const uint64_t k2 = slot_of(w2, b2);
+                    if (lane == 0) red2[wid] = k2;
+                    qb_lds_barrier();
+                    kb = qb_min_winners<NW>(red2, lane);
+                }
+                dib = (uint32_t)(kb >> 32);
+                i = (int)((uint32_t)kb >> 1);
+                ti = i & (TB - 1);
+                ei = i / TB;
+                s = (kb & 1) ? -1 : 1;
             }
-            dib = (uint32_t)(kb >> 32);
-            i = (int)((uint32_t)kb >> 1);
-            s = (kb & 1) ? -1 : 1;
         }
-        const int32_t dmove = (int32_t)(dib - bias);
-        OV += dmove;
-        gap += dmove;
         // the row base is uniform (scalar registers); each lane adds its own
         // 32-bit chunk offsets
-        int32_t q[EPT];
-        tabu_row<QT, EPT, TB>(Qt + (uint32_t)i * (uint32_t)ldp, (uint32_t)tid, q);
-        // h_j += s Q_ji  =>  D_j += S_j s Q_ji, applied to the key above its
-        // element bits (the owner is patched below)
-        if (s > 0) {
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) Kb[e] += (uint32_t)__mul24(q[e], S[e]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) Kb[e] -= (uint32_t)__mul24(q[e], S[e]);
-        }
-        const int ti = i & (TB - 1);
-        if (tid == ti) {
-            // the owner patches its element ei and bumps the counters without
-            // waiting on LDS
-            const int ei = i / TB;
-            xb ^= 1u << ei;
-            pb ^= 1u << ei;
-            atomicAdd(&Ts[i], 1);
-            Ls[i] = step;
-            // tenure from this step on (the remaining tenure of an aspirated
-            // variable carries over), and the new key: minus the old move value
-            auto tabu_until = [&](int32_t u) { return step + max(max(u - (step - 1), 0) + tenure - 1, 0); };
-            auto new_key = [&](int32_t un, uint32_t e) {
-                uint32_t kn = ((2u * bias - dib) << EB) | e;
-                if (un > step) {
-                    kn |= TBIT;
+        Row q;
+        q.load(rows, (uint32_t)i * pitch, (uint32_t)tid);
+
+        // Everything else of the step while the row is on its way.
+        const int rel = hist[(step - tenure + 1) & (TABU_RING - 1)];
+        gap += (int32_t)(dib - bias);
+        if ((ti >> 6) == wu) {
+            // the owner patches its element: minus the old move value (the
+            // row's diagonal is zero in the Tabu copy, so the update below
+            // leaves it)
+            const bool mine = lane == (ti & 63);
+            const uint32_t old = Kb[ei], sgn = S[ei];
+            Kb[ei] = tabu_held(mine ? ((2u * bias - dib) << EB) | (uint32_t)ei | tnew : old);
+            S[ei] = tabu_held(sgn ^ (mine ? SX << (Row::BITS * (ei % Row::EPW)) : 0u));
+            const uint32_t bit = mine ? 1u << ei : 0u;
+            xb ^= bit;
+            pb ^= bit;
+            if (__builtin_expect(far | (__ballot((int32_t)old < 0) >> (ti & 63) & 1u), 0)) {
+                if (mine && tnew) {
+                    int32_t left = 0;
+                    if (old & TBIT) {
+                        const int64_t u = (late >> ei) & 1u ? (int64_t)Tout[ro + i] : (int64_t)Ls[i] + tenure - 1;
+                        left = max((int32_t)min(u, (int64_t)alpha + 1) - (step - 1), 0);
+                    }
+                    // alpha + 1 is past the last step
+                    const int32_t un = (int32_t)min((int64_t)step + left + tenure - 1, (int64_t)alpha + 1);
+                    Tout[ro + i] = un;
+                    late |= 1u << ei;
                     nexp = min(nexp, un);
                 }
-                return kn;
-            };
-            auto patch = [&](auto ec) {
-                constexpr int e = decltype(ec)::value;
-                if constexpr (e < EPT) {
-                    const int32_t Un = tabu_until(U[e]);
-                    U[e] = Un;
-                    S[e] = -S[e];
-                    Kb[e] = new_key(Un, (uint32_t)e);
-                }
-            };
-            static_assert(EPT <= 16, "sixteen cases");
-            if constexpr (EPT <= 10) {
-                // the uniform ei indexes the register arrays (selects over
-                // the few elements)
-                const int32_t Un = tabu_until(U[ei]);
-                U[ei] = Un;
-                S[ei] = -S[ei];
-                Kb[ei] = new_key(Un, (uint32_t)ei);
-            } else switch (ei) {
-                // a scalar branch per element: an index into the larger
-                // arrays would send them to scratch memory
-#define QB_TABU_CASE(c) \
-    case c: patch(std::integral_constant<int, c>{}); break;
-                QB_TABU_CASE(0) QB_TABU_CASE(1) QB_TABU_CASE(2) QB_TABU_CASE(3)
-                QB_TABU_CASE(4) QB_TABU_CASE(5) QB_TABU_CASE(6) QB_TABU_CASE(7)
-                QB_TABU_CASE(8) QB_TABU_CASE(9) QB_TABU_CASE(10) QB_TABU_CASE(11)
-                QB_TABU_CASE(12) QB_TABU_CASE(13) QB_TABU_CASE(14) QB_TABU_CASE(15)
-#undef QB_TABU_CASE
-            default: break;
+            }
+            if (mine) Ls[i] = step;
+        }
+        // the books by another wave than the owner's
+        if (((ti >> 6) + NW / 2) % NW == wu && lane == 0) {
+            lds_inc(&Ts[i]);
+            hist[step & (TABU_RING - 1)] = i;
+        }
+        {
+            // the variable that is free again at the next step
+            const int v = __builtin_amdgcn_readfirstlane(rel);
+            if (v >= 0 && ((v >> 6) & (NW - 1)) == wu) {
+                const int ev = v / TB;
+                const uint32_t kv = Kb[ev];
+                Kb[ev] = tabu_held(lane == (v & 63) && !((late >> ev) & 1u) ? kv & ~TBIT : kv);
+            }
+        }
+        if (__builtin_expect(__ballot(step >= nexp) != 0, 0)) {
+            nexp = 0x7fffffff;
+#pragma unroll 1
+            for (int e = 0; e < EPT; ++e) {
+                const bool wait = (late >> e) & 1u;
+                const int32_t u = wait ? Tout[ro + e * TB + tid] : 0x7fffffff;
+                const uint32_t kv = Kb[e];
+                Kb[e] = tabu_held(u <= step ? kv & ~TBIT : kv);
+                late &= u <= step ? ~(1u << e) : ~0u;
+                nexp = min(nexp, u <= step ? 0x7fffffff : u);
             }
         }
         if ((int32_t)((uint64_t)gap >> 32) < 0) {
             // a new best: x_min is the current x
+            OVmin += gap;
             gap = 0;
             pb = 0;
         }
+        tbk = asp && (uint64_t)gap < bias ? (bias - (uint32_t)gap) << EB : 0u;
+        // the signs follow the flip's direction
+        if (s != turned) {
+            turned = s;
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) S[e] ^= SX << (Row::BITS * (e % Row::EPW));
+        }
+
+        // h_j += s Q_ji  =>  D_j += S_j s Q_ji, applied to the key above its
+        // element bits
+        tabu_arrive(q.w);
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) Kb[e] = q.mad(e, S[e], Kb[e]);
     };
 
     int step = 1;
@@ -333,7 +399,6 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
         one_step(step + 1, red[0]);
     }
     if (step == alpha) one_step(step, red[1]);
-    const int64_t OVmin = OV - gap;
 
     // field of the final x from D, then moved to x_min = x ^ pb row by row
     int32_t h[EPT];
@@ -343,7 +408,9 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
         h[e] = 0;
         if (j < n) {
             const int32_t qjj = Q16[(int64_t)j * n + j];
-            h[e] = ((int32_t)(((Kb[e] & ~TBIT) >> EB) - bias) - qjj) * (S[e] >> EB) / 4;
+            h[e] = ((int32_t)(((Kb[e] & ~TBIT) >> EB) - bias) - qjj) * (((xb >> e) & 1u) ? -2 : 2) / 4;
+            // the diagonal's part of the move to x_min (zero in the Tabu copy)
+            if ((pb >> e) & 1u) h[e] += ((xb >> e) & 1u) ? -qjj : qjj;
         }
     }
 #pragma unroll
@@ -357,13 +424,21 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
         }
         __syncthreads();
         const int cnt = lcount;
-        for (int u = 0; u < cnt; ++u) {
-            const int32_t v = list[u];
-            const int32_t sg = v < 0 ? -1 : 1;
-            int32_t q[EPT];
-            tabu_row<QT, EPT, TB>(Qt + (uint32_t)(v < 0 ? -v - 1 : v - 1) * (uint32_t)ldp, (uint32_t)tid, q);
+        if (tid < 3) list[cnt + tid] = 0;
+        __syncthreads();
+        for (int u = 0; u < cnt; u += 4) {           // four rows on their way at once
+            Row q[4];
+            int32_t sg[4];
 #pragma unroll
-            for (int e2 = 0; e2 < EPT; ++e2) h[e2] += sg * q[e2];
+            for (int k = 0; k < 4; ++k) {
+                const int32_t v = __builtin_amdgcn_readfirstlane(list[u + k]);
+                sg[k] = v > 0 ? 1 : v < 0 ? -1 : 0;
+                q[k].load(rows, (uint32_t)(v > 0 ? v - 1 : v < 0 ? -v - 1 : 0) * pitch, (uint32_t)tid);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int e2 = 0; e2 < EPT; ++e2) h[e2] = (int32_t)q[k].mad(e2, Row::place(e2, sg[k]), (uint32_t)h[e2]);
         }
         __syncthreads();
     }
@@ -399,9 +474,13 @@ qb_status launch_keyed(const QT *Qt, int ldp, qb_problem P, int z, uint8_t *X, i
 {
     if (2 * dmax + 1 >= (int64_t)(0x7FFFFFFFu >> qb_ceil_log2(EPT))) return QB_E_RANGE;
     const uint32_t bias = (uint32_t)dmax;
-    if (((2 * dmax + 1) << qb_ceil_log2(EPT)) < (int64_t(1) << (31 - TabuShape<TB>::WB)))
-        return launch_one<EPT, QT, true, TB>(Qt, ldp, P, z, X, H, E, alpha, tenure, asp, T, LF, bias, s);
-    return launch_one<EPT, QT, false, TB>(Qt, ldp, P, z, X, H, E, alpha, tenure, asp, T, LF, bias, s);
+    // one wave has no winners to compare, and int8 moves always fit
+    // (|D| <= 127 (2 n + 1): 2^23 for n = 16384)
+    constexpr bool always = TB == 64 || (sizeof(QT) == 1 && TB < QB_TABU_THREADS);
+    if (TB < QB_TABU_THREADS && ((2 * dmax + 1) << qb_ceil_log2(EPT)) < (int64_t(1) << (31 - TabuShape<TB>::WB)))
+        return launch_one<EPT, QT, (TB < QB_TABU_THREADS), TB>(Qt, ldp, P, z, X, H, E, alpha, tenure, asp, T, LF, bias,
+                                                              s);
+    return launch_one<EPT, QT, always, TB>(Qt, ldp, P, z, X, H, E, alpha, tenure, asp, T, LF, bias, s);
 }
 
 template <typename QT>
@@ -414,10 +493,14 @@ qb_status launch_tabu(qb_problem P, const QT *Qt, int ldp, int z, uint8_t *X, in
 #define QB_T(K, W)                                                                                 \
     if (ept == K && tb == W)                                                                      \
         return launch_keyed<K, QT, W>(Qt, ldp, P, z, X, H, E, alpha, tenure, asp, T, LF, dmax, s);
-    // eight waves only where qb_tabu_threads picks them (5, 6 or 10 elements)
-    QB_T(5, 512) QB_T(6, 512) QB_T(10, 512)
-    QB_T(1, 1024) QB_T(2, 1024) QB_T(3, 1024) QB_T(4, 1024) QB_T(5, 1024) QB_T(6, 1024)
-    QB_T(7, 1024) QB_T(8, 1024) QB_T(10, 1024) QB_T(12, 1024) QB_T(14, 1024) QB_T(16, 1024)
+    QB_T(1, 64) QB_T(2, 64) QB_T(4, 64) QB_T(8, 64) QB_T(12, 64) QB_T(16, 64) QB_T(20, 64) QB_T(24, 64)
+    QB_T(8, 256) QB_T(12, 256) QB_T(16, 256) QB_T(20, 256) QB_T(24, 256) QB_T(28, 256) QB_T(32, 256)
+    QB_T(20, 512) QB_T(24, 512) QB_T(28, 512) QB_T(32, 512)
+    // move values past the others' keys: 16-bit weights only
+    if constexpr (sizeof(QT) == 2) {
+        QB_T(1, 1024) QB_T(2, 1024) QB_T(3, 1024) QB_T(4, 1024) QB_T(5, 1024) QB_T(6, 1024)
+        QB_T(7, 1024) QB_T(8, 1024) QB_T(10, 1024) QB_T(12, 1024) QB_T(14, 1024) QB_T(16, 1024)
+    }
 #undef QB_T
     return QB_E_CAPACITY;
 }
