@@ -48,6 +48,12 @@
 // of its leaves that holds every leaf free at t, except possibly those whose
 // tenure ends exactly at t (they are still in slots and enter the minimum
 // from there), and no leaf tabu at t.
+//
+// What bounds it: one wave's chain of about 230 instructions and four LDS
+// round trips per step.  Hence no 64-bit address and no branch between the
+// winner and its row (a buffer load by the row's scalar offset), and the rare
+// branches out of the way: 0.774 -> 0.748 us per step (n = 20,000 of degree
+// 4, 16 solutions, tenure 133).
 #include "qb_internal.h"
 
 namespace {
@@ -191,6 +197,11 @@ __global__ void __launch_bounds__(64) k_tabu_tree(const uint32_t *__restrict__ e
     constexpr int32_t GCAP = 1 << 30;
     int32_t gap = 0;
     const int ten1 = max(tenure - 1, 0);
+    // a row of the ELL by its scalar offset, lanes past its width out of range
+    // and so 0, without a branch (0x27000: raw 32-bit elements)
+    const __amdgpu_buffer_rsrc_t rows =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(ell), 0, (uint32_t)n * (uint32_t)W * 4u, 0x27000);
+    const uint32_t erow = lane < W ? 4u * (uint32_t)lane : 0x80000000u;
 
     // steps in batches of 64 (batch b: steps 64 b .. 64 b + 63), the flip
     // counts sent at the end of each
@@ -232,7 +243,7 @@ __global__ void __launch_bounds__(64) k_tabu_tree(const uint32_t *__restrict__ e
             }
             fm = min(fm, cm);
             uint32_t tov = NONE;   // least tabu key among the overflow bits
-            if (ovf > 0) {
+            if (__builtin_expect(ovf > 0, 0)) {
                 // tabu variables without a slot: scan their bits
                 int freed = 0;
                 for (int w = lane; w < NXW; w += 64) {
@@ -256,7 +267,7 @@ __global__ void __launch_bounds__(64) k_tabu_tree(const uint32_t *__restrict__ e
                 ovf -= wave_sum(freed);
             }
             uint32_t best = min_uniform(fm);
-            if (best == NONE) {
+            if (__builtin_expect(best == NONE, 0)) {
                 // everything tabu and nothing aspirates: the least tabu key
                 uint32_t tm = tov;
 #pragma unroll
@@ -267,8 +278,7 @@ __global__ void __launch_bounds__(64) k_tabu_tree(const uint32_t *__restrict__ e
             const uint32_t dib = best >> IB;
 
             // the winner's row, in flight while its own leaf and node are redone
-            uint32_t wd = 0u;
-            if (lane < W) wd = ell[(int64_t)i * W + lane];
+            const uint32_t wd = __builtin_amdgcn_raw_buffer_load_b32(rows, erow, (uint32_t)(i * W) * 4u, 0);
 
             // the winner's node, read once: its lane gives x_i and U_i, and the
             // node is recomputed from registers with the winner's leaf rewritten
@@ -303,7 +313,7 @@ __global__ void __launch_bounds__(64) k_tabu_tree(const uint32_t *__restrict__ e
             OV += dmove;
             gap += dmove;
             const bool improved = gap < 0;
-            if (improved) {
+            if (__builtin_expect(improved, 0)) {
                 gap = 0;
                 OVmin = OV;
             } else {
@@ -316,7 +326,7 @@ __global__ void __launch_bounds__(64) k_tabu_tree(const uint32_t *__restrict__ e
             // (lane li's leaf of the node is i itself: jl == i there)
             *one_lane(L, L.dl + jl, lane, li) = (uint16_t)dl_l;
             *one_lane(L, L.Ul + jl, lane, li) = ul_l;
-            if (improved) {   // x_min is the current x
+            if (__builtin_expect(improved, 0)) {   // x_min is the current x
                 for (int w = lane; w < NXW; w += 64) L.pw[w] = 0u;
             } else {
                 __hip_atomic_fetch_xor(one_lane(L, L.pw + (i >> 5), lane, 0), bit, __ATOMIC_RELAXED,
@@ -340,11 +350,11 @@ __global__ void __launch_bounds__(64) k_tabu_tree(const uint32_t *__restrict__ e
             const bool was_tabu = Ui >= step, now_tabu = Un > step;
             int ps = -1, plane = 0, sjv = i;
             int32_t suv = Un;
-            if (!was_tabu) {
+            if (__builtin_expect(!was_tabu, 1)) {
                 if (now_tabu) {
                     plane = step & 63;
                     ps = 0;
-                    if (__builtin_amdgcn_readlane(sj[0], plane) != SENT) {
+                    if (__builtin_expect(__builtin_amdgcn_readlane(sj[0], plane) != SENT, 0)) {
                         ps = -1;
                         // the highest row with an empty slot: row r is the ring
                         // row again after r rotations, and row 0 (this batch's
@@ -393,7 +403,7 @@ __global__ void __launch_bounds__(64) k_tabu_tree(const uint32_t *__restrict__ e
                 const int trow = lane == plane ? ps : -1;   // the row this lane rewrites, if any
                 sj[0] = trow == 0 ? sjv : sj[0];
                 su[0] = trow == 0 ? suv : su[0];
-                if (S > 1 && ps > 0) {
+                if (__builtin_expect(S > 1 && ps > 0, 0)) {
 #pragma unroll
                     for (int s = 1; s < S; ++s) {
                         const bool mine = trow == s;
