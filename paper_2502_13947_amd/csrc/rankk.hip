@@ -5,6 +5,8 @@
 // of one solution and a range of rows; the changed variables of the range are
 // compacted into an LDS list and every thread adds +-Q[j][i] for its four
 // consecutive columns (Q is symmetric, so column j of Q is row j).
+#include <algorithm>
+
 #include "qb_internal.h"
 
 namespace {
@@ -97,19 +99,28 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int RM_K = 128, RM_N = 128, RM_LD = RM_K + 16;
 
-// 16 bytes of a row of dX (rows start at any byte: one load at any alignment)
-__device__ __forceinline__ v4i load_a16(const int8_t *__restrict__ row, int kk, int n)
+// 16 bytes of a row of dX at kk, zero from n on, without a branch on a lane:
+// the row's last 16 bytes shifted into place where kk + 16 passes its end
+// (rows start at any byte: one load at any alignment)
+__device__ __forceinline__ v4i load_end16(const int8_t *__restrict__ row, int kk, int n)
 {
-    v4i v = {0, 0, 0, 0};
-    if (kk + 16 <= n) {
-        __builtin_memcpy(&v, row + kk, 16);
-    } else if (kk < n) {
-        uint32_t w[4] = {0, 0, 0, 0};
+    uint64_t w[2] = {0, 0};
+    if (n >= 16) {
+        const int at = min(kk, n - 16), sh = 8 * min(kk - at, 16);
+        __builtin_memcpy(w, row + at, 16);
+        const uint64_t lo = sh < 64 ? w[0] >> sh : 0, up = sh == 0 || sh >= 128 ? 0 : sh < 64 ? w[1] << (64 - sh)
+                                                                                          : w[1] >> (sh - 64);
+        w[0] = lo | up;
+        w[1] = sh < 64 ? w[1] >> sh : 0;
+    } else {
 #pragma unroll
-        for (int b = 0; b < 16; ++b)
-            if (kk + b < n) w[b >> 2] |= (uint32_t)(uint8_t)row[kk + b] << (8 * (b & 3));
-        v = v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+        for (int b = 0; b < 16; ++b) {
+            const uint64_t v = (uint8_t)row[min(kk + b, n - 1)];
+            w[b >> 3] |= kk + b < n ? v << (8 * (b & 7)) : 0;
+        }
     }
+    v4i v;
+    __builtin_memcpy(&v, w, 16);
     return v;
 }
 
@@ -130,19 +141,33 @@ __global__ void __launch_bounds__(128 * WM) k_rankk_mfma(const int8_t *__restric
     const int nstep = (min(kchunk, kpad - kbeg) + RM_K - 1) / RM_K;
     const int r16 = lane & 15, g = lane >> 4;
     const int lrow = tid >> 3, lcol = (tid & 7) * 16;
+    // rows past the last solution or variable are read as the first one: their
+    // sums are not stored
+    const int8_t *ap[NA], *bp[NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int p = m0 + lrow + i * RPT;
+        ap[i] = dX + (int64_t)(p < z ? p : 0) * n;
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int c = n0 + lrow + i * RPT;
+        bp[i] = Qp + (int64_t)(c < n ? c : 0) * ldp;
+    }
     struct Stage { v4i a[NA], b[NB]; };
     auto fetch = [&](Stage &st, int step) {
         const int kk = kbeg + step * RM_K + lcol;
+        if (kbeg + (step + 1) * RM_K <= n) {         // no condition on a lane, so no wait between the loads
 #pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int p = m0 + lrow + i * RPT;
-            st.a[i] = step < nstep && p < z ? load_a16(dX + (int64_t)p * n, kk, n) : v4i{0, 0, 0, 0};
-        }
+            for (int i = 0; i < NA; ++i) __builtin_memcpy(&st.a[i], ap[i] + kk, 16);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const int c = n0 + lrow + i * RPT;
-            st.b[i] = step < nstep && c < n && kk < kpad
-                          ? *reinterpret_cast<const v4i *>(Qp + (int64_t)c * ldp + kk) : v4i{0, 0, 0, 0};
+            for (int i = 0; i < NB; ++i) st.b[i] = *reinterpret_cast<const v4i *>(bp[i] + kk);
+        } else if (step < nstep) {                   // the step that holds the rows' ends
+#pragma unroll
+            for (int i = 0; i < NA; ++i) st.a[i] = load_end16(ap[i], kk, n);
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+                st.b[i] = *reinterpret_cast<const v4i *>(bp[i] + min(kk, kpad - 16));   // past n: times 0
         }
     };
     auto stash = [&](const Stage &st, int buf) {
@@ -184,7 +209,7 @@ __global__ void __launch_bounds__(128 * WM) k_rankk_mfma(const int8_t *__restric
         stash(s1, 1);
         fetch(s1, step + 3);
         qb_lds_barrier();
-        multiply(1);                                 // zeros past the last step
+        if (step + 1 < nstep) multiply(1);
         stash(s0, 0);
     }
     // 16x16 result layout: lane holds rows 4g..4g+3 of column r16
@@ -202,17 +227,18 @@ __global__ void __launch_bounds__(128 * WM) k_rankk_mfma(const int8_t *__restric
 }
 
 template <int WM>
-qb_status rankk_mfma_go(qb_problem P, int z, const int8_t *dX, int32_t *H, hipStream_t s)
+qb_status rankk_mfma_go(qb_problem P, int z, const int8_t *dX, int32_t *H, int ncu, hipStream_t s)
 {
     const int n = P->n;
     const int gx = (n + RM_N - 1) / RM_N, gy = (z + 64 * WM - 1) / (64 * WM);
     const int nk = (n + RM_K - 1) / RM_K;
     // LDS holds one workgroup of WM = 4 on a compute unit, two of the others
-    int ncu = 0;
-    QB_TRY_HIP(qb_cu_count(&ncu));
     const int fit = ncu * (WM == 4 ? 1 : 2);
     int split = fit / (gx * gy);
-    split = split < 1 ? 1 : split > nk ? nk : split;
+    // six splits at most: past that the atomics cost more than the rows save
+    // (n = 2500, 256 solutions: 20, 20 and 32 us with 4, 6 and 12 splits;
+    // n = 12,000, 40 solutions: 40 and 36 us with 4 and 6)
+    split = std::min({std::max(split, 1), nk, 6});
     const int steps = (nk + split - 1) / split;
     k_rankk_mfma<WM><<<dim3(gx, gy, (nk + steps - 1) / steps), 128 * WM, 0, s>>>(
         dX, n, z, (const int8_t *)P->Qp, P->ldp, H, RM_K * steps);
@@ -259,8 +285,15 @@ qb_status qb_field_ell_launch(qb_problem P, int z, const uint8_t *X, int32_t *H,
 
 qb_status qb_rankk_mfma_launch(qb_problem P, int z, const int8_t *dX, int32_t *H, hipStream_t s)
 {
-    return z <= 64 ? rankk_mfma_go<1>(P, z, dX, H, s)
-           : z <= 128 ? rankk_mfma_go<2>(P, z, dX, H, s) : rankk_mfma_go<4>(P, z, dX, H, s);
+    // all solutions in one workgroup, unless six splits of so few workgroups
+    // leave half the card idle
+    int ncu = 0;
+    QB_TRY_HIP(qb_cu_count(&ncu));
+    const int64_t gx = (P->n + RM_N - 1) / RM_N;
+    int wm = z <= 64 ? 1 : z <= 128 ? 2 : 4;
+    while (wm > 1 && 12 * gx * ((z + 64 * wm - 1) / (64 * wm)) < ncu) wm >>= 1;
+    return wm == 1 ? rankk_mfma_go<1>(P, z, dX, H, ncu, s)
+           : wm == 2 ? rankk_mfma_go<2>(P, z, dX, H, ncu, s) : rankk_mfma_go<4>(P, z, dX, H, ncu, s);
 }
 
 extern "C" qb_status qb_rankk(qb_problem P, int32_t z, const int8_t *dX_d, int32_t *H_d, int32_t variant,
