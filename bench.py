@@ -429,7 +429,7 @@ def measure_workload(a, name, steps, warmup, cpu_seconds, headline):
         mavg = float(np.sum(w["job_m"])) / b.J
         row_bytes = mavg * esz
         adds = mavg
-        placement = "tiles of m <= 512 in LDS, m = 1024 rows streamed from L2/HBM"
+        placement = "columns in registers (m <= 512), accepted rows of m = 1024 from L2/HBM"
     lds_bytes = accepts * row_bytes
     valu_ops = attempts * ANNEAL_OPS_PER_ATTEMPT + accepts * adds
     t_lds = lds_bytes / (LDS_PEAK_GBS * 1e9)
