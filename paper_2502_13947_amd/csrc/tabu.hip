@@ -30,8 +30,8 @@
 // owner's patch, the tabu lists, the books -- placed while the row is on its
 // way.  One variable at most is released per step without any scan: the ring
 // of flips names it.  Against sixteen waves that scanned their own release
-// steps and patched after the row: n = 7000, 256 solutions 1.01 -> 0.75 us
-// per step, n = 2500 0.75 -> 0.60, n = 1000 0.63 -> 0.51, n = 256 0.60 -> 0.45.
+// steps and patched after the row: n = 7000, 256 solutions 0.99 -> 0.70 us
+// per step, n = 2500 0.75 -> 0.59, n = 1000 0.63 -> 0.50, n = 256 0.60 -> 0.46.
 #include <algorithm>
 
 #include "qb_internal.h"
@@ -116,6 +116,26 @@ struct TabuRow {
         }
     }
 };
+
+// The winning slot of NWV (wave minimum << WB | wave in the low word, the
+// wave's mark in the high one), uniform; all ones when every slot is empty.
+template <int NWV>
+__device__ __forceinline__ void tabu_pick32(const uint64_t *slot, int lane, uint32_t &key, uint32_t &hi)
+{
+    static_assert(NWV <= 16, "one row of 16 lanes");
+    // every lane reads a slot (lanes past NWV repeat them): no exec mask
+    const uint64_t v = slot[lane & (NWV - 1)];
+    uint32_t lo = (uint32_t)v;
+    lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+    lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+    // eight slots: the upper half of the row repeats the lower
+    if constexpr (NWV > 4)
+        lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x124, 0xF, 0xF, false));  // row_ror 4
+    if constexpr (NWV > 8)
+        lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x128, 0xF, 0xF, false));  // row_ror 8
+    key = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+    hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)(key & (NWV - 1)));
+}
 
 // The words of a row are not looked at before this point.
 template <int N>
@@ -236,24 +256,24 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
         const uint32_t fk = (uint32_t)max((int32_t)m1, -1);    // KNONE when every key is tabu
         const uint32_t tk = (uint32_t)m2 ^ TBIT;               // >= TBIT (never aspirates) when none is
         const uint32_t best = min(fk, tk < tbk ? tk : KNONE);
+        // a lane's half of its wave's winner slot, should it win: its number
+        // and its best variable's x
+        auto mark_of = [&](uint32_t bsel) { return (uint32_t)lane << 1 | ((xb >> (bsel & EMASK)) & 1u); };
+        const uint32_t mark = mark_of(best);
         const uint32_t wmin = qb_wave_min_u32_b(best);
         // lowest index among the minimal moves of the wave: the lowest lane
         // holding the minimal key (move, element)
         auto lane_of = [&](uint32_t wm, uint32_t bsel) { return (int)__builtin_ctzll(__ballot(bsel == wm)); };
-        auto x_of = [&](uint32_t wm, int L) {
-            return ((uint32_t)__builtin_amdgcn_readlane((int)xb, L) >> (wm & EMASK)) & 1u;
-        };
         // the wave's winner slot for minimum key wm among the lanes' keys bsel
-        // (a whole-wave call); padding keys never win a K32 slot
-        auto slot_of = [&](uint32_t wm, uint32_t bsel) -> uint64_t {
-            const int L = lane_of(wm, bsel);
-            const uint32_t xw = x_of(wm, L);
-            if constexpr (K32) {
-                if (wm >= (1u << (31 - WB))) return ~0ull;
-                return ((uint64_t)(((uint32_t)L << 1) | xw) << 32) | ((wm << WB) | (uint32_t)wu);
-            } else {
-                return qb_tabu_winner(wm >> EB, (int)(wm & EMASK) * TB + wu * 64 + L, xw);
-            }
+        // (a whole-wave call); padding keys, and no key at all, never win a
+        // K32 slot
+        auto slot_of = [&](uint32_t wm, uint32_t bsel, uint32_t mark) -> uint64_t {
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)mark, lane_of(wm, bsel));
+            if constexpr (K32)
+                return ((uint64_t)hi << 32) | (wm >= (1u << (31 - WB)) ? ~0u : (wm << WB) | (uint32_t)wu);
+            else
+                return wm == KNONE ? ~0ull
+                                   : qb_tabu_winner(wm >> EB, (int)(wm & EMASK) * TB + wu * 64 + (int)(hi >> 1), hi & 1u);
         };
         uint32_t dib;
         int i, ei, ti;                             // the variable, its element and thread
@@ -267,25 +287,25 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
                 wm = qb_wave_min_u32_b(bsel);
             }
             ti = lane_of(wm, bsel);
-            s = x_of(wm, ti) ? -1 : 1;
             dib = wm >> EB;
             ei = (int)(wm & EMASK);
+            s = ((uint32_t)__builtin_amdgcn_readlane((int)xb, ti) >> ei) & 1u ? -1 : 1;
             i = ei * TB + ti;
         } else {
-            uint64_t wkey = ~0ull;
-            if (wmin != KNONE) wkey = slot_of(wmin, best);
+            const uint64_t wkey = slot_of(wmin, best, mark);
             if (lane == 0) slots[wid] = wkey;
             qb_lds_barrier();
             if constexpr (K32) {
-                uint32_t key = 0, hi = 0;
-                if (__builtin_expect(!qb_pick32<NW>(slots, lane, key, hi), 0)) {
+                uint32_t key, hi;
+                tabu_pick32<NW>(slots, lane, key, hi);
+                if (__builtin_expect(key == ~0u, 0)) {
                     // every variable is tabu and none aspirates: argmin over all of them
                     const uint32_t b2 = min(fk, tk);
                     const uint32_t w2 = qb_wave_min_u32_b(b2);
-                    const uint64_t k2 = slot_of(w2, b2);
+                    const uint64_t k2 = slot_of(w2, b2, mark_of(b2));
                     if (lane == 0) red2[wid] = k2;
                     qb_lds_barrier();
-                    qb_pick32<NW>(red2, lane, key, hi);
+                    tabu_pick32<NW>(red2, lane, key, hi);
                 }
                 const uint32_t wm = key >> WB;
                 dib = wm >> EB;
@@ -299,7 +319,7 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
                     // every variable is tabu and none aspirates: argmin over all of them
                     const uint32_t b2 = min(fk, tk);
                     const uint32_t w2 = qb_wave_min_u32_b(b2);
-                    const uint64_t k2 = slot_of(w2, b2);
+                    const uint64_t k2 = slot_of(w2, b2, mark_of(b2));
                     if (lane == 0) red2[wid] = k2;
                     qb_lds_barrier();
                     kb = qb_min_winners<NW>(red2, lane);
@@ -379,6 +399,9 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
             pb = 0;
         }
         tbk = asp && (uint64_t)gap < bias ? (bias - (uint32_t)gap) << EB : 0u;
+        // ready before the row is (one wave alone does better with the
+        // compiler's order)
+        if constexpr (NW > 1) asm volatile("" : "+s"(tbk));
         // the signs follow the flip's direction
         if (s != turned) {
             turned = s;
