@@ -49,10 +49,11 @@ static inline __host__ __device__ int32_t qb_ell_val(uint32_t w) { return (int32
 
 // Threads of the dense Tabu workgroup for n variables.  A step is a serial
 // chain that every wave walks, so few waves with many variables each win: at
-// n = 1000 one, four and eight waves take 0.51, 0.55 and 0.61 us per step, at
-// n = 1500 0.54, 0.57 and 0.62, at n = 2000 0.60, 0.58 and 0.63, and at n =
-// 7000 four, eight and sixteen waves 0.75, 0.74 and 0.88 (int8).  Thirty-two
-// variables per thread are the most the kernel keeps in registers.
+// n = 1000 one and four waves take 0.50 and 0.55 us per step, at n = 1280 0.53
+// and 0.55, at n = 1500 0.55 both, at n = 2000 0.60 and 0.56 (eight 0.63), and
+// at n = 7000 four, eight and sixteen 0.75, 0.74 and 0.88 with int8 (four and
+// eight 0.73 and 0.78 once four had their last 5 %).  Thirty-two variables per
+// thread are the most the kernel keeps in registers.
 // QB_TABU_THREADS is the width for move values too large for the others' keys.
 #define QB_TABU_THREADS 1024
 static inline __host__ __device__ int qb_tabu_threads(int n)
@@ -66,7 +67,7 @@ static inline __host__ __device__ int qb_tabu_threads(int n)
 static inline int qb_tabu_ept(int n, int tb)
 {
     static const int wide[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16};
-    static const int deep[] = {1, 2, 4, 8, 12, 16, 20, 24, 28, 32};
+    static const int deep[] = {1, 2, 4, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32};   // whole words past 16 bytes
     if (tb == QB_TABU_THREADS) {
         for (int e : wide)
             if (n <= tb * e) return e;

@@ -31,7 +31,7 @@
 // way.  One variable at most is released per step without any scan: the ring
 // of flips names it.  Against sixteen waves that scanned their own release
 // steps and patched after the row: n = 7000, 256 solutions 0.99 -> 0.70 us
-// per step, n = 2500 0.75 -> 0.59, n = 1000 0.63 -> 0.50, n = 256 0.60 -> 0.46.
+// per step, n = 2500 0.75 -> 0.58, n = 1000 0.63 -> 0.50, n = 256 0.60 -> 0.46.
 #include <algorithm>
 
 #include "qb_internal.h"
@@ -516,8 +516,10 @@ qb_status launch_tabu(qb_problem P, const QT *Qt, int ldp, int z, uint8_t *X, in
 #define QB_T(K, W)                                                                                 \
     if (ept == K && tb == W)                                                                      \
         return launch_keyed<K, QT, W>(Qt, ldp, P, z, X, H, E, alpha, tenure, asp, T, LF, dmax, s);
-    QB_T(1, 64) QB_T(2, 64) QB_T(4, 64) QB_T(8, 64) QB_T(12, 64) QB_T(16, 64) QB_T(20, 64) QB_T(24, 64)
-    QB_T(8, 256) QB_T(12, 256) QB_T(16, 256) QB_T(20, 256) QB_T(24, 256) QB_T(28, 256) QB_T(32, 256)
+    QB_T(1, 64) QB_T(2, 64) QB_T(4, 64) QB_T(6, 64) QB_T(8, 64) QB_T(10, 64) QB_T(12, 64) QB_T(14, 64)
+    QB_T(16, 64) QB_T(20, 64) QB_T(24, 64)
+    QB_T(8, 256) QB_T(10, 256) QB_T(12, 256) QB_T(14, 256) QB_T(16, 256) QB_T(20, 256) QB_T(24, 256)
+    QB_T(28, 256) QB_T(32, 256)
     QB_T(20, 512) QB_T(24, 512) QB_T(28, 512) QB_T(32, 512)
     // move values past the others' keys: 16-bit weights only
     if constexpr (sizeof(QT) == 2) {

@@ -37,8 +37,9 @@ def _qubo(n, lim, density, seed):
 
 
 @pytest.mark.parametrize("lim", [127, 300])
-@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 256, 257, 512, 513, 768, 769, 1024, 1025, 1280, 1281, 1536,
-                               1537, 2048, 2049, 3072, 3073, 4097, 5121, 6145, 7169, 8192, 8193, 10241])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 256, 257, 384, 385, 512, 513, 640, 641, 768, 769, 896, 897, 1024, 1025, 1280, 1281, 1536,
+                               1537, 2048, 2049, 2560, 2561, 3072, 3073,
+                               3584, 3585, 4097, 5121, 6145, 7169, 8192, 8193, 10241])
 def test_tabu_every_workgroup_and_row(n, lim):
     """Both sides of every variables-per-thread count, one, four and eight
     waves, 8-bit and 16-bit rows; whole numbers, exact."""
