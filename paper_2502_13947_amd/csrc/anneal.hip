@@ -1230,23 +1230,35 @@ __global__ void k_reset_queues(int *__restrict__ q, int n)
 }
 
 // Whether the speculating kernel is the automatic choice.  It takes a job's
-// sweep 2.5 to 3 times as fast as the other kernels (m = 64, 128, 256, 512,
-// 1024, 256 jobs, R = 1, int8: 0.5, 0.8, 1.5, 2.9, 8 us a sweep against 1.5,
-// 1.9, 3.4, 6.7, 23), but with a workgroup of its own for every replica; the
-// one-wave kernels pack the R replicas of a job into one workgroup and, once
-// R replicas of many jobs fill the chip several times over, finish more
-// replicas a microsecond (m = 300, 256 jobs x 16: 12.6 us a sweep for all
-// against 26).  The lines, in replicas per compute unit, lie where both took
-// the same time.  At mp = 1024 it takes 170 us to load the columns (256
-// jobs; 84 us before the others' first sweep), which 8 sweeps win back.
+// sweep 2 to 3 times as fast as the other kernels (256 jobs of ranked
+// variables, R = 1, int8, m = 64, 128, 256, 512, 1024: 0.34, 0.35, 0.32, 0.35
+// and 0.42 of their time), but with a workgroup of its own for every replica;
+// the others pack the R replicas of a job into one workgroup, and finish more
+// replicas a microsecond once many replicas share a compute unit (m = 1024,
+// R = 2, 1024 jobs of random variables: 17 us a sweep for all against 63).
+// A line is the number of replicas per compute unit up to which it is taken,
+// for up to r replicas a job and for more; it lies where the geometric mean of
+// its time over theirs, for jobs of ranked variables after a Tabu run and for
+// jobs of random ones, passes 1 (n = 2500, J = 1 to 4096, R = 1 to 16; the
+// first accept two to three times as often, which costs only the others).
+// At int8, m = 512 and R = 4, for instance, one, two and four replicas per
+// unit take 0.28, 0.55 and 1.08 of their time ranked, 0.70, 1.33 and 2.56
+// random; at R = 2, 0.30 and 0.59 and no more, and 0.58 and 1.15.  At int16,
+// mp = 512 and R = 1: 0.48, 0.81 and 1.14, and 0.70, 1.16 and 1.50.
+// Where it reads rows from memory it loads its columns first (mp = 1024: 100
+// to 170 us before the first sweep against 20 to 45), which takes a few
+// sweeps to win back.
 bool spec_pays(int cls, bool int8_tile, int njobs, int R, int nsw)
 {
-    static const int per_cu[2][QB_NCLASS] = {{0, 2, 6, 8, 12}, {4, 5, 8, 12, 12}};
+    constexpr int ALL = 1 << 20;
+    static const struct { int r, few, many; } line[2][QB_NCLASS] = {
+        {{16, 0, 0}, {1, 2, 1}, {4, ALL, 2}, {1, ALL, 6}, {16, 6, 6}},
+        {{1, ALL, 2}, {3, ALL, 2}, {4, ALL, 4}, {8, ALL, 12}, {16, 12, 12}}};
+    if (cls == (int8_tile ? 0 : 1) && nsw < (R == 1 ? 8 : int8_tile ? 32 : 12)) return false;
+    const auto &l = line[int8_tile ? 1 : 0][cls];
+    const int lim = R <= l.r ? l.few : l.many;
     int ncu = 0;
-    if (cls == 0 && nsw < 8) return false;
-    if (R < 4 || qb_cu_count(&ncu) != hipSuccess) return true;
-    int lim = per_cu[int8_tile ? 1 : 0][cls];
-    if (int8_tile && cls == 1 && R == 4) lim = 3;      // four replicas still fit the multi-wave kernel
+    if (lim == ALL || qb_cu_count(&ncu) != hipSuccess) return lim > 0;
     return (int64_t)njobs * R <= (int64_t)lim * ncu;
 }
 

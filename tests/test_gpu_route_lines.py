@@ -1,0 +1,81 @@
+"""The lines between two kernels of one call: on either side the call has to
+take about as long as the better one.  Each case was measured at least 2
+times too long on the wrong side, and is held to 1.6 times."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def qb():
+    from paper_2502_13947_amd import qb as m
+    return m
+
+
+def best_ms(f, reps=5):
+    """Least time of a call among `reps` (after one to warm up)."""
+    f()
+    torch.cuda.synchronize()
+    best = float("inf")
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+def dense_problem(n, lim, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    Q = torch.triu(torch.randint(-lim, lim + 1, (n, n), generator=g, device=DEV, dtype=torch.int16))
+    return qb().Problem((Q + torch.triu(Q, 1).T).contiguous())
+
+
+def solutions(P, z, seed, alpha):
+    """z solutions after `alpha` Tabu steps, with their fields and statistics."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    X = torch.randint(0, 2, (z, P.n), generator=g, device=DEV, dtype=torch.uint8)
+    H = torch.zeros((z, P.n), dtype=torch.int32, device=DEV)
+    E = torch.zeros(z, dtype=torch.int64, device=DEV)
+    T, LF = torch.zeros_like(H), torch.zeros_like(H)
+    qb().field(P, X, H)
+    qb().energy(X, H, E)
+    qb().tabu(P, X, H, E, alpha, max(1, P.n // 150), True, T, LF)
+    return X, H, E, T, LF
+
+
+@pytest.mark.parametrize("lim,m,J,R", [(100, 700, 1024, 2), (100, 1000, 1024, 3), (1000, 400, 1024, 2),
+                                       (1000, 512, 1024, 3), (100, 256, 256, 8)])
+def test_many_replicas_take_the_packed_annealer(lim, m, J, R):
+    """qb_anneal without a plan, against the plan that packs a job's replicas
+    into one workgroup (QB_ANNEAL_MULTI_WAVE): results equal, and no slower."""
+    n, k, nsw = 4 * m + 100, 4, 40
+    z = J // k
+    P = dense_problem(n, lim, 5)
+    X, H, _, _, _ = solutions(P, z, 3, n)
+    b = qb().Batch(n, z, np.repeat(np.arange(z), k), np.full(J, m))
+    g = torch.Generator(device=DEV)
+    g.manual_seed(8)
+    order = torch.argsort(torch.rand((z, n), generator=g, device=DEV), dim=1).to(torch.int32).contiguous()
+    qb().select(b, order)
+    tiles = torch.zeros(b.tile_elems, dtype=qb().tile_dtype(P), device=DEV)
+    F0 = torch.zeros(b.total, dtype=torch.int32, device=DEV)
+    y0 = torch.zeros(b.total, dtype=torch.uint8, device=DEV)
+    qb().extract(P, b, X, H, tiles, F0, y0)
+    thr = torch.as_tensor(qb().threshold_table(nsw, 10, 0.25 * P.sigma, 0.002 * P.sigma), device=DEV)
+    out, ms = [], []
+    for kernel in (0, 1):
+        b.set_plan(kernel=[kernel] * 5)
+        Y = torch.zeros(b.total * R, dtype=torch.uint8, device=DEV)
+        e = torch.zeros(J * R, dtype=torch.int64, device=DEV)
+        ms.append(best_ms(lambda: qb().anneal(b, tiles, F0, y0, thr, R, 5, 0, Y, e, 10)))
+        out.append((Y, e))
+    print(f"lim {lim} m {m} J {J} R {R}: {ms[0]:.3f} ms, packed {ms[1]:.3f} ms", flush=True)
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert ms[0] <= 1.6 * ms[1]
