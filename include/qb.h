@@ -207,8 +207,8 @@ typedef struct {
  *   kernel[c]: the kernel of size class c (c = 0..4 for padded widths
  *     mp = 1024, 512, 256, 128, 64): QB_ANNEAL_AUTO (a workgroup per
  *     replica that decides blocks of positions at once and repairs them,
- *     unless many jobs have R >= 4 replicas or the class is mp = 1024 with
- *     int16 tiles or under 8 sweeps: then the next two), QB_ANNEAL_MULTI_WAVE
+ *     unless so many replicas share a compute unit, or so few sweeps follow,
+ *     that the next kernel is faster), QB_ANNEAL_MULTI_WAVE
  *     (a replica spread over up to four waves where its replicas fit one
  *     workgroup, else one wave per replica; also the automatic choice while
  *     qb_set_anneal_wait_limit differs from its default),
@@ -217,8 +217,8 @@ typedef struct {
  *     LDS only: int8 mp <= 512, int16 mp <= 128), or
  *     QB_ANNEAL_MULTI_WAVE_GLOBAL (a replica over up to four waves reading
  *     the tile rows from global memory: int8 mp = 1024, int16 mp = 512,
- *     R = 1); a kernel that cannot run the class falls back to the automatic
- *     choice;
+ *     R = 1); the last two fall back to the automatic choice for a class
+ *     that they cannot run;
  *   persistent: 1 = each class runs as a persistent grid of
  *     wgs_per_cu workgroups per compute unit (at most one per job) that pull
  *     the class's jobs from an atomic queue; 0 = one workgroup per job;

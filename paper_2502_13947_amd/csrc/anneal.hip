@@ -1262,49 +1262,71 @@ bool spec_pays(int cls, bool int8_tile, int njobs, int R, int nsw)
     return (int64_t)njobs * R <= (int64_t)lim * ncu;
 }
 
+// The kernel that a size class runs under plan kernel `want`.  A named kernel
+// without an instantiation for the class, its type or R gives way to the
+// automatic choice (QB_ANNEAL_MULTI_WAVE: to one wave per replica).
+enum class Runs { spec, multi_wave, one_wave, one_wave_reg };
+
+Runs anneal_runs(int want, int cls, bool int8_tile, int njobs, int R, int nsw)
+{
+    // replicas that the multi-wave kernels fit into a workgroup
+    static const int rmax[2][QB_NCLASS] = {{0, 1, AnnealMw<4, int16_t, 0>::RMAX, AnnealMw<2, int16_t, 0>::RMAX, 0},
+                                           {1, AnnealMw<8, int8_t, 1>::RMAX, AnnealMw<4, int8_t, 0>::RMAX,
+                                            AnnealMw<2, int8_t, 0>::RMAX, 0}};
+    // (list tags of 24 bits)
+    const bool multi = R <= rmax[int8_tile ? 1 : 0][cls] && (int64_t)nsw * qb_ms_of_class(cls) + 1 < (int64_t(1) << 24);
+    const bool global_rows = cls == (int8_tile ? 0 : 1);
+    const bool reg = cls >= (int8_tile ? 1 : 3);
+    if (want == QB_ANNEAL_MULTI_WAVE_GLOBAL) want = global_rows && multi ? QB_ANNEAL_MULTI_WAVE : QB_ANNEAL_AUTO;
+    if (want == QB_ANNEAL_ONE_WAVE_REG && !reg) want = QB_ANNEAL_AUTO;
+    if (want == QB_ANNEAL_ONE_WAVE_REG) return Runs::one_wave_reg;
+    if (want == QB_ANNEAL_AUTO && g_wait_limit.load(std::memory_order_relaxed) == MW_WAIT_DEFAULT &&
+        spec_pays(cls, int8_tile, njobs, R, nsw))
+        return Runs::spec;
+    return want != QB_ANNEAL_ONE_WAVE && multi ? Runs::multi_wave : Runs::one_wave;
+}
+
 bool dispatch_anneal(int cls, bool int8_tile, int nblocks, int R, hipStream_t s, const int32_t *jobs, qb_batch b,
                      const void *tiles, const int32_t *F0, const uint8_t *y0, int nsw, int B, const int32_t *thr,
                      uint64_t seed, uint32_t inst_base, const qb_iter *it, uint8_t *Y, int64_t *e)
 {
-    const int want = b->plan.kernel[cls];
-    // (rows in global memory: the one class whose multi-wave kernel reads them there)
-    const bool global_rows = cls == (int8_tile ? 0 : 1);
-    if ((want == QB_ANNEAL_AUTO || (want == QB_ANNEAL_MULTI_WAVE_GLOBAL && !global_rows)) &&
-        g_wait_limit.load(std::memory_order_relaxed) == MW_WAIT_DEFAULT && spec_pays(cls, int8_tile, nblocks, R, nsw) &&
-        qb_launch_anneal_spec(cls, int8_tile, nblocks, R, s, jobs, b, tiles, F0, y0, nsw, B, thr, seed, inst_base, it,
-                              Y, e))
-        return true;
 #define QB_ARGS nblocks, R, s, jobs, b, tiles, F0, y0, nsw, B, thr, seed, inst_base, it, Y, e
-    // the one-wave kernel with the couplings in registers, where the plan asks for it
-    if (want == QB_ANNEAL_ONE_WAVE_REG) {
+    switch (anneal_runs(b->plan.kernel[cls], cls, int8_tile, nblocks, R, nsw)) {
+    case Runs::spec:
+        return qb_launch_anneal_spec(cls, int8_tile, nblocks, R, s, jobs, b, tiles, F0, y0, nsw, B, thr, seed,
+                                     inst_base, it, Y, e);
+    case Runs::one_wave_reg:
         if (int8_tile) {
             switch (cls) {
-            case 1: if (launch_anneal_dc<8, int8_t, 1>(QB_ARGS)) return true; break;
-            case 2: if (launch_anneal_dc<4, int8_t, 0>(QB_ARGS)) return true; break;
-            case 3: if (launch_anneal_dc<2, int8_t, 0>(QB_ARGS)) return true; break;
-            case 4: if (launch_anneal_dc<1, int8_t, 0>(QB_ARGS)) return true; break;
+            case 1: return launch_anneal_dc<8, int8_t, 1>(QB_ARGS);
+            case 2: return launch_anneal_dc<4, int8_t, 0>(QB_ARGS);
+            case 3: return launch_anneal_dc<2, int8_t, 0>(QB_ARGS);
+            case 4: return launch_anneal_dc<1, int8_t, 0>(QB_ARGS);
             }
         } else {
             switch (cls) {
-            case 3: if (launch_anneal_dc<2, int16_t, 0>(QB_ARGS)) return true; break;
-            case 4: if (launch_anneal_dc<1, int16_t, 0>(QB_ARGS)) return true; break;
+            case 3: return launch_anneal_dc<2, int16_t, 0>(QB_ARGS);
+            case 4: return launch_anneal_dc<1, int16_t, 0>(QB_ARGS);
             }
         }
-    }
-    // the multi-wave kernel where its replicas fit one workgroup
-    if (want != QB_ANNEAL_ONE_WAVE && int8_tile) {
-        switch (cls) {
-        case 0: if (launch_anneal_mw_g<16, int8_t>(QB_ARGS)) return true; break;
-        case 1: if (launch_anneal_mw<8, int8_t, 1>(QB_ARGS)) return true; break;
-        case 2: if (launch_anneal_mw<4, int8_t, 0>(QB_ARGS)) return true; break;
-        case 3: if (launch_anneal_mw<2, int8_t, 0>(QB_ARGS)) return true; break;
+        return false;
+    case Runs::multi_wave:
+        if (int8_tile) {
+            switch (cls) {
+            case 0: return launch_anneal_mw_g<16, int8_t>(QB_ARGS);
+            case 1: return launch_anneal_mw<8, int8_t, 1>(QB_ARGS);
+            case 2: return launch_anneal_mw<4, int8_t, 0>(QB_ARGS);
+            case 3: return launch_anneal_mw<2, int8_t, 0>(QB_ARGS);
+            }
+        } else {
+            switch (cls) {
+            case 1: return launch_anneal_mw_g<8, int16_t>(QB_ARGS);
+            case 2: return launch_anneal_mw<4, int16_t, 0>(QB_ARGS);
+            case 3: return launch_anneal_mw<2, int16_t, 0>(QB_ARGS);
+            }
         }
-    } else if (want != QB_ANNEAL_ONE_WAVE) {
-        switch (cls) {
-        case 1: if (launch_anneal_mw_g<8, int16_t>(QB_ARGS)) return true; break;
-        case 2: if (launch_anneal_mw<4, int16_t, 0>(QB_ARGS)) return true; break;
-        case 3: if (launch_anneal_mw<2, int16_t, 0>(QB_ARGS)) return true; break;
-        }
+        return false;
+    case Runs::one_wave: break;
     }
     if (int8_tile) {
         switch (cls) {

@@ -50,12 +50,10 @@ def solutions(P, z, seed, alpha):
     return X, H, E, T, LF
 
 
-@pytest.mark.parametrize("lim,m,J,R", [(100, 700, 1024, 2), (100, 1000, 1024, 3), (1000, 400, 1024, 2),
-                                       (1000, 512, 1024, 3), (100, 256, 256, 8)])
-def test_many_replicas_take_the_packed_annealer(lim, m, J, R):
-    """qb_anneal without a plan, against the plan that packs a job's replicas
-    into one workgroup (QB_ANNEAL_MULTI_WAVE): results equal, and no slower."""
-    n, k, nsw = 4 * m + 100, 4, 40
+def dense_jobs(lim, m, J):
+    """J jobs of m random variables, four of a solution, extracted after a
+    Tabu run."""
+    n, k = 4 * m + 100, 4
     z = J // k
     P = dense_problem(n, lim, 5)
     X, H, _, _, _ = solutions(P, z, 3, n)
@@ -68,14 +66,36 @@ def test_many_replicas_take_the_packed_annealer(lim, m, J, R):
     F0 = torch.zeros(b.total, dtype=torch.int32, device=DEV)
     y0 = torch.zeros(b.total, dtype=torch.uint8, device=DEV)
     qb().extract(P, b, X, H, tiles, F0, y0)
+    return P, b, tiles, F0, y0
+
+
+def two_plans(lim, m, J, R, nsw, kernels):
+    """Times of the annealer under two plan kernels; the results are equal."""
+    P, b, tiles, F0, y0 = dense_jobs(lim, m, J)
     thr = torch.as_tensor(qb().threshold_table(nsw, 10, 0.25 * P.sigma, 0.002 * P.sigma), device=DEV)
     out, ms = [], []
-    for kernel in (0, 1):
+    for kernel in kernels:
         b.set_plan(kernel=[kernel] * 5)
         Y = torch.zeros(b.total * R, dtype=torch.uint8, device=DEV)
         e = torch.zeros(J * R, dtype=torch.int64, device=DEV)
         ms.append(best_ms(lambda: qb().anneal(b, tiles, F0, y0, thr, R, 5, 0, Y, e, 10)))
         out.append((Y, e))
-    print(f"lim {lim} m {m} J {J} R {R}: {ms[0]:.3f} ms, packed {ms[1]:.3f} ms", flush=True)
+    print(f"lim {lim} m {m} J {J} R {R} kernels {kernels}: {ms[0]:.3f} and {ms[1]:.3f} ms", flush=True)
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
-    assert ms[0] <= 1.6 * ms[1]
+    return ms
+
+
+@pytest.mark.parametrize("lim,m,J,R", [(100, 700, 1024, 2), (100, 1000, 1024, 3), (1000, 400, 1024, 2),
+                                       (1000, 512, 1024, 3), (100, 256, 256, 8)])
+def test_many_replicas_take_the_packed_annealer(lim, m, J, R):
+    """qb_anneal without a plan, against the plan that packs a job's replicas
+    into one workgroup (QB_ANNEAL_MULTI_WAVE)."""
+    auto, packed = two_plans(lim, m, J, R, 40, (0, 1))
+    assert auto <= 1.6 * packed
+
+
+@pytest.mark.parametrize("lim,m,kernel", [(100, 1000, 3), (1000, 300, 3)])
+def test_plan_kernel_without_the_class_is_the_automatic_one(lim, m, kernel):
+    """A plan that names a kernel which cannot run the class."""
+    named, auto = two_plans(lim, m, 64, 1, 200, (kernel, 0))
+    assert named <= 1.6 * auto
