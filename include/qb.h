@@ -211,7 +211,7 @@ typedef struct {
  *     that the next kernel is faster), QB_ANNEAL_MULTI_WAVE
  *     (a replica spread over up to four waves where its replicas fit one
  *     workgroup, else one wave per replica; also the automatic choice while
- *     qb_set_anneal_wait_limit differs from its default),
+ *     the limit of qb_set_anneal_wait_limit is 0),
  *     QB_ANNEAL_ONE_WAVE, or QB_ANNEAL_ONE_WAVE_REG (one wave per replica
  *     holding the current diagonal block's couplings in registers; tiles in
  *     LDS only: int8 mp <= 512, int16 mp <= 128), or
@@ -312,9 +312,10 @@ qb_status qb_anneal(qb_batch b, const void *tile_d, int32_t int8_tile, const int
  * annealers (qb_anneal): a wave that reads a list word `polls` times without
  * finding it written gives up, and its replica reports e = INT64_MIN (Y then
  * holds an unfinished state).  Default 2^24 polls (about a second); 0 makes
- * every wait that does not succeed at once give up.  While the limit is not
- * the default, QB_ANNEAL_AUTO takes those kernels.  Process-wide, takes
- * effect at the next launch; for tests of that path.  QB_E_ARG if polls < 0. */
+ * every wait that does not succeed at once give up, and QB_ANNEAL_AUTO take
+ * those kernels; any other value leaves the automatic choice as it is.
+ * Process-wide, takes effect at the next launch; for tests of that path.
+ * QB_E_ARG if polls < 0. */
 qb_status qb_set_anneal_wait_limit(int32_t polls);
 
 /* Sparse sub-QUBOs (eq. 4 on a problem made by qb_problem_create_csr).  Same

@@ -1280,7 +1280,8 @@ Runs anneal_runs(int want, int cls, bool int8_tile, int njobs, int R, int nsw)
     if (want == QB_ANNEAL_MULTI_WAVE_GLOBAL) want = global_rows && multi ? QB_ANNEAL_MULTI_WAVE : QB_ANNEAL_AUTO;
     if (want == QB_ANNEAL_ONE_WAVE_REG && !reg) want = QB_ANNEAL_AUTO;
     if (want == QB_ANNEAL_ONE_WAVE_REG) return Runs::one_wave_reg;
-    if (want == QB_ANNEAL_AUTO && g_wait_limit.load(std::memory_order_relaxed) == MW_WAIT_DEFAULT &&
+    // (a limit of 0 asks for the kernels whose waits it makes give up)
+    if (want == QB_ANNEAL_AUTO && g_wait_limit.load(std::memory_order_relaxed) != 0 &&
         spec_pays(cls, int8_tile, njobs, R, nsw))
         return Runs::spec;
     return want != QB_ANNEAL_ONE_WAVE && multi ? Runs::multi_wave : Runs::one_wave;
