@@ -508,15 +508,16 @@ void qb_graph_destroy(void *graph_exec);
 qb_status qb_autotune_rankk(qb_problem P, int32_t z, const int8_t *dX_d, const int32_t *H_d, int32_t reps,
                             int32_t *variant_out, float *ms_out, void *stream);
 /* Plan autotuner of qb_anneal (the batching schedule): coordinate descent
- * over qb_anneal_plan on the given jobs -- the kernel of each size class
- * present (largest first), the persistent job queue with its grid
- * (workgroups per compute unit) and its order (longest job first or job
- * order), and the consumers' loads in flight -- timing `reps` launches of
- * each candidate after a warm-up launch.  Every candidate must give the same
- * Y and e as the batch's plan on entry (else QB_E_STATE).  The fastest plan
- * is left set on the batch and returned in *plan_out (its mean time in
- * *ms_out; both optional).  Not a hot call: it allocates scratch and
- * synchronises `stream`. */
+ * over qb_anneal_plan on the given jobs -- the kernels of each size class
+ * present (largest first; each kernel once, whatever plans name it), the
+ * persistent job queue with its grid (workgroups per compute unit) and its
+ * order (longest job first or job order), and, where a class reads rows from
+ * memory, the consumers' loads in flight -- timing `reps` launches of each
+ * candidate after a warm-up launch.  Every candidate must give the same Y and
+ * e as the batch's plan on entry (else QB_E_STATE).  The fastest plan is left
+ * set on the batch and returned in *plan_out (its mean time in *ms_out; both
+ * optional).  Not a hot call: it allocates scratch and synchronises
+ * `stream`. */
 qb_status qb_autotune_anneal(qb_batch b, const void *tile_d, int32_t int8_tile, const int32_t *F0_d,
                              const uint8_t *y0_d, int32_t nsw, int32_t B, const int32_t *thr_d, int32_t R,
                              uint64_t seed, uint32_t inst_base, int32_t reps, qb_anneal_plan *plan_out, float *ms_out,

@@ -1262,12 +1262,14 @@ bool spec_pays(int cls, bool int8_tile, int njobs, int R, int nsw)
     return (int64_t)njobs * R <= (int64_t)lim * ncu;
 }
 
+using Runs = qb_anneal_runs;
+
+}  // namespace
+
 // The kernel that a size class runs under plan kernel `want`.  A named kernel
 // without an instantiation for the class, its type or R gives way to the
 // automatic choice (QB_ANNEAL_MULTI_WAVE: to one wave per replica).
-enum class Runs { spec, multi_wave, one_wave, one_wave_reg };
-
-Runs anneal_runs(int want, int cls, bool int8_tile, int njobs, int R, int nsw)
+qb_anneal_runs qb_anneal_runs_of(int want, int cls, bool int8_tile, int njobs, int R, int nsw)
 {
     // replicas that the multi-wave kernels fit into a workgroup
     static const int rmax[2][QB_NCLASS] = {{0, 1, AnnealMw<4, int16_t, 0>::RMAX, AnnealMw<2, int16_t, 0>::RMAX, 0},
@@ -1287,12 +1289,14 @@ Runs anneal_runs(int want, int cls, bool int8_tile, int njobs, int R, int nsw)
     return want != QB_ANNEAL_ONE_WAVE && multi ? Runs::multi_wave : Runs::one_wave;
 }
 
+namespace {
+
 bool dispatch_anneal(int cls, bool int8_tile, int nblocks, int R, hipStream_t s, const int32_t *jobs, qb_batch b,
                      const void *tiles, const int32_t *F0, const uint8_t *y0, int nsw, int B, const int32_t *thr,
                      uint64_t seed, uint32_t inst_base, const qb_iter *it, uint8_t *Y, int64_t *e)
 {
 #define QB_ARGS nblocks, R, s, jobs, b, tiles, F0, y0, nsw, B, thr, seed, inst_base, it, Y, e
-    switch (anneal_runs(b->plan.kernel[cls], cls, int8_tile, nblocks, R, nsw)) {
+    switch (qb_anneal_runs_of(b->plan.kernel[cls], cls, int8_tile, nblocks, R, nsw)) {
     case Runs::spec:
         return qb_launch_anneal_spec(cls, int8_tile, nblocks, R, s, jobs, b, tiles, F0, y0, nsw, B, thr, seed,
                                      inst_base, it, Y, e);

@@ -209,6 +209,9 @@ static inline int qb_grid(const qb_batch_s *b, int njobs)
 bool qb_launch_anneal_spec(int cls, bool int8_tile, int njobs, int R, hipStream_t s, const int32_t *jobs, qb_batch b,
                            const void *tiles, const int32_t *F0, const uint8_t *y0, int nsw, int B, const int32_t *thr,
                            uint64_t seed, uint32_t inst_base, const qb_iter *it, uint8_t *Y, int64_t *e);
+// The annealer kernels, and the one that a size class runs under a plan kernel.
+enum class qb_anneal_runs { spec, multi_wave, one_wave, one_wave_reg };
+qb_anneal_runs qb_anneal_runs_of(int want, int cls, bool int8_tile, int njobs, int R, int nsw);
 // Compute units of the current device (cached per device).
 hipError_t qb_cu_count(int *out);
 

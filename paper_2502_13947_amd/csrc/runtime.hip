@@ -203,7 +203,7 @@ extern "C" qb_status qb_autotune_anneal_ell(qb_batch b, int32_t W, const uint32_
 
 // Plan autotuner of the dense annealer (qb_anneal): coordinate descent over
 // the result-invariant knobs of qb_anneal_plan on the caller's batch -- the
-// kernel of each size class present (largest class first), then the
+// kernels of each size class present (largest class first), then the
 // persistent queue with its grid and its order, then the consumers' loads in
 // flight -- timing `reps` launches of each candidate after one warm-up
 // launch and keeping a change only when it is faster.  Every candidate's Y
@@ -297,8 +297,13 @@ extern "C" qb_status qb_autotune_anneal(qb_batch b, const void *tile_d, int32_t 
     for (int c = 0; c < QB_NCLASS && rc == QB_OK; ++c) {
         if (b->cls_end[c] <= b->cls_begin[c]) continue;
         const qb_anneal_plan base = best;
-        for (int k : {QB_ANNEAL_MULTI_WAVE_GLOBAL, QB_ANNEAL_ONE_WAVE, QB_ANNEAL_ONE_WAVE_REG, QB_ANNEAL_AUTO}) {
-            if (k == base.kernel[c]) continue;
+        auto runs = [&](int k) {
+            return 1u << (int)qb_anneal_runs_of(k, c, int8_tile != 0, b->cls_end[c] - b->cls_begin[c], R, nsw);
+        };
+        uint32_t timed = runs(base.kernel[c]);   // each kernel once, whatever plan names it
+        for (int k : {QB_ANNEAL_AUTO, QB_ANNEAL_MULTI_WAVE, QB_ANNEAL_ONE_WAVE, QB_ANNEAL_ONE_WAVE_REG}) {
+            if (timed & runs(k)) continue;
+            timed |= runs(k);
             qb_anneal_plan p = base;
             p.kernel[c] = k;
             trial(p);
@@ -324,7 +329,10 @@ extern "C" qb_status qb_autotune_anneal(qb_batch b, const void *tile_d, int32_t 
         p.lpt = 1 - p.lpt;
         trial(p);
     }
-    {
+    // the one class whose multi-wave kernel reads rows from memory
+    const int gc = int8_tile ? 0 : 1, gj = b->cls_end[gc] - b->cls_begin[gc];
+    if (rc == QB_OK && gj > 0 &&
+        qb_anneal_runs_of(best.kernel[gc], gc, int8_tile != 0, gj, R, nsw) == qb_anneal_runs::multi_wave) {
         qb_anneal_plan p = best;
         p.depth = p.depth == 8 ? 16 : 8;
         trial(p);

@@ -71,3 +71,13 @@ def test_a_wait_limit_leaves_the_automatic_choice_alone():
     assert (got[1] == want[1]).all() and (got[2] == want[2]).all()
     for g, w in zip(got[0], want[0]):
         assert (g == w).all()
+
+
+def test_autotuner_tries_a_kernel_once():
+    """No plan names a kernel by two numbers, and the loads in flight stay as
+    they are where no chosen kernel reads them."""
+    J = Jobs(1500, 2, [512, 256, 128, 64], True, 71, 5)
+    for seed in range(6):
+        J.b.set_plan(sleep_after=16, depth=8, kernel=[0] * 5, persistent=0, wgs_per_cu=1, lpt=1)
+        plan, _ = qb().autotune_anneal(J.b, J.tiles, J.F0, J.y0, J.thr_d, 1, seed, 0, B, reps=1)
+        assert all(k in (0, 1, 2, 3) for k in plan["kernel"]) and plan["depth"] == 8, plan
