@@ -81,3 +81,38 @@ def test_autotuner_tries_a_kernel_once():
         J.b.set_plan(sleep_after=16, depth=8, kernel=[0] * 5, persistent=0, wgs_per_cu=1, lpt=1)
         plan, _ = qb().autotune_anneal(J.b, J.tiles, J.F0, J.y0, J.thr_d, 1, seed, 0, B, reps=1)
         assert all(k in (0, 1, 2, 3) for k in plan["kernel"]) and plan["depth"] == 8, plan
+
+
+# every plan kernel on every class: those that take accepts one by one (1, 2,
+# 3 and, where it reads rows from memory, 4), the replicas on both sides of
+# what the multi-wave kernels fit into a workgroup (1; 4 of mp = 256 and 512;
+# 8 of mp = 128), and the fall-backs of 3 and 4
+@pytest.mark.parametrize("kernel", [1, 2, 3, 4])
+@pytest.mark.parametrize("R", [1, 3, 4, 5, 9, 16])
+@pytest.mark.parametrize("int8", [True, False])
+def test_plan_kernels_match_the_oracle(int8, R, kernel):
+    """Y, e and the accept counts of a plan kernel on jobs of every class."""
+    print("plan kernels", int8, R, kernel, flush=True)
+    J = Jobs(2200, 1, [1024, 500, 256, 100, 64, 37], int8, 81, 5)
+    J.b.set_plan(kernel=[kernel] * 5)
+    Y, e, n = J.run(R, 19, 6)
+    for q in range(J.b.J):
+        Yo, eo, no = J.oracle(q, R, 19, 6)
+        assert (Y[q] == Yo).all() and (e[q] == eo).all() and (n[q] == no).all(), (q, J.b.sizes[q])
+
+
+@pytest.mark.parametrize("int8,m,J,R", [(True, 64, 200, 16), (True, 128, 200, 16), (True, 200, 210, 5),
+                                        (True, 300, 130, 4), (True, 520, 140, 4), (False, 64, 400, 4),
+                                        (False, 128, 400, 4), (False, 250, 110, 5), (False, 300, 90, 3),
+                                        (False, 500, 260, 2)])
+def test_automatic_choice_past_its_lines(int8, m, J, R):
+    """Enough replicas that the automatic choice is not the kernel with a
+    workgroup for each: a sample of the jobs against the oracle."""
+    print("past the lines", int8, m, J, R, flush=True)
+    per = 4
+    z = -(-J // per)
+    A = Jobs(per * m + 20, z, [m] * per, int8, 91, 3)
+    Y, e, n = A.run(R, 23, 4)
+    for q in range(0, A.b.J, 7):
+        Yo, eo, no = A.oracle(q, R, 23, 4)
+        assert (Y[q] == Yo).all() and (e[q] == eo).all() and (n[q] == no).all(), q
