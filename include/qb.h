@@ -136,10 +136,11 @@ qb_status qb_best(int32_t n, int32_t z, const uint8_t *X_d, const int64_t *E_d, 
  * decremented.  On return X[p] = x_min, H[p] = Q x_min, E[p] = OV_min
  * (E[p] must hold x^T Q x on entry), T[p][j] = flips of j, LF[p][j] = the
  * 1-based step of j's last flip (0 if none).  A tenure beyond alpha + 1
- * is taken as alpha + 1 (the same search).  Capacity: n <= 16384 (dense
- * problems; one workgroup of 512 or 1024 threads per solution, fixed when
- * the problem is created from n and the range of the move values, every
- * step reads one row of Q) or, for sparse problems (every step reads the
+ * is taken as alpha + 1 (the same search).  T_d is also scratch during the
+ * call.  Capacity: n <= 16384 (dense problems; one workgroup of 64 to 512
+ * threads per solution, 1024 for the widest moves, fixed when the problem is
+ * created from n and the range of the move values, every step reads one row
+ * of Q) or, for sparse problems (every step reads the
  * flipped variable's off-diagonal entries only), n <= 25856 on the tree
  * kernel and n <= 20480 on the lane kernel (qb_problem_set_tabu_variant);
  * QB_E_CAPACITY beyond.  QB_E_RANGE when |Q_kk| + 2 max_k eta_k

@@ -160,14 +160,16 @@ __device__ __forceinline__ void lds_inc(int32_t *p)
     asm volatile("ds_add_u32 %0, %1" ::"v"(a), "v"(1) : "memory");
 }
 
-constexpr int TABU_RING = 1024;   // flips remembered for the release of their variables
+// A flip in the ring: beyond 8192 variables two bytes, for more of them.
+template <int TB>
+using TabuFlip = std::conditional_t<(TB > 256), uint16_t, int32_t>;
 
 template <int EPT, typename QT, bool K32, int TB>
 __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp, const int16_t *__restrict__ Q16,
                                              int n, uint8_t *__restrict__ X, int32_t *__restrict__ H,
                                              int64_t *__restrict__ E, int alpha, int tenure, int asp,
                                              int32_t *__restrict__ Tout, int32_t *__restrict__ LFout,
-                                             uint32_t bias)
+                                             uint32_t bias, int ring)
 {
     constexpr int NW = TabuShape<TB>::NW, WB = TabuShape<TB>::WB;
     constexpr int EB = qb_ceil_log2(EPT);           // bits of the element index
@@ -175,10 +177,10 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
     __shared__ uint64_t red[2][NW];
     __shared__ uint64_t red2[NW];
     __shared__ int32_t list[TB + 3];             // padded to a multiple of 4 with 0 = no row
-    __shared__ int32_t hist[TABU_RING];
     __shared__ int lcount;
-    extern __shared__ int32_t tl[];              // [0,n): flips, [n,2n): last-flip step
-    int32_t *Ts = tl, *Ls = tl + n;
+    extern __shared__ int32_t tl[];              // the ring; [n] flips, [n] last-flip steps
+    TabuFlip<TB> *hist = reinterpret_cast<TabuFlip<TB> *>(tl);
+    int32_t *Ts = tl + ring * (int)sizeof(TabuFlip<TB>) / 4, *Ls = Ts + n;
 
     const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int64_t ro = (int64_t)p * n;
@@ -230,12 +232,16 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
     const int wu = __builtin_amdgcn_readfirstlane(wid);
     // A variable flipped at step t is tabu through step t + tenure - 1, plus
     // the tenure that was left when it aspirated.  Without such a rest the
-    // ring of flips names it when its time is over (-1: nobody).  With one, or
-    // with a tenure past the ring, it is `late`: its last tabu step waits in
-    // Tout (scratch until the end) and nexp.
-    const uint32_t far = tenure >= TABU_RING;
+    // ring of flips names it when its time is over (all ones: nobody).  With
+    // one, or with a tenure past the ring, it is `late`: its last tabu step
+    // waits in Tout (scratch until the end) and nexp.  A tenure that reaches
+    // the last step releases nobody.
+    const int rmask = ring - 1;
+    const bool never = tenure >= alpha;
+    const uint32_t vend = never ? 0u : 0xFFFFu;   // the ring releases variables below
+    const uint32_t far = !never && tenure >= ring;
     const uint32_t tnew = tenure >= 2 ? TBIT : 0u;
-    for (int t = tid; t < TABU_RING; t += TB) hist[t] = -1;
+    for (int t = tid; t < ring; t += TB) hist[t] = (TabuFlip<TB>)-1;
     // aspiration: a tabu key k aspirates when (k >> EB) < OV_min - OV + bias,
     // that is k < tbk (zero when nothing can aspirate)
     uint32_t tbk = asp ? bias << EB : 0u;
@@ -337,7 +343,7 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
         q.load(rows, (uint32_t)i * pitch, (uint32_t)tid);
 
         // Everything else of the step while the row is on its way.
-        const int rel = hist[(step - tenure + 1) & (TABU_RING - 1)];
+        const uint32_t rel = (uint32_t)hist[(step - tenure + 1) & rmask];
         gap += (int32_t)(dib - bias);
         if ((ti >> 6) == wu) {
             // the owner patches its element: minus the old move value (the
@@ -351,7 +357,7 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
             xb ^= bit;
             pb ^= bit;
             if (__builtin_expect(far | (__ballot((int32_t)old < 0) >> (ti & 63) & 1u), 0)) {
-                if (mine && tnew) {
+                if (mine && tnew && !never) {
                     int32_t left = 0;
                     if (old & TBIT) {
                         const int64_t u = (late >> ei) & 1u ? (int64_t)Tout[ro + i] : (int64_t)Ls[i] + tenure - 1;
@@ -369,27 +375,42 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
         // the books by another wave than the owner's
         if (((ti >> 6) + NW / 2) % NW == wu && lane == 0) {
             lds_inc(&Ts[i]);
-            hist[step & (TABU_RING - 1)] = i;
+            hist[step & rmask] = (TabuFlip<TB>)i;
         }
         {
             // the variable that is free again at the next step
-            const int v = __builtin_amdgcn_readfirstlane(rel);
-            if (v >= 0 && ((v >> 6) & (NW - 1)) == wu) {
+            const int v = __builtin_amdgcn_readfirstlane((int)rel);
+            if ((uint32_t)v < vend && ((v >> 6) & (NW - 1)) == wu) {
                 const int ev = v / TB;
                 const uint32_t kv = Kb[ev];
                 Kb[ev] = tabu_held(lane == (v & 63) && !((late >> ev) & 1u) ? kv & ~TBIT : kv);
             }
         }
         if (__builtin_expect(__ballot(step >= nexp) != 0, 0)) {
+            // the elements that are late in any lane, four at a time: their
+            // steps are read together
             nexp = 0x7fffffff;
+            uint32_t any = late;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) any |= (uint32_t)__shfl_xor((int)any, o, 64);
+            any = (uint32_t)__builtin_amdgcn_readfirstlane((int)any);
 #pragma unroll 1
-            for (int e = 0; e < EPT; ++e) {
-                const bool wait = (late >> e) & 1u;
-                const int32_t u = wait ? Tout[ro + e * TB + tid] : 0x7fffffff;
-                const uint32_t kv = Kb[e];
-                Kb[e] = tabu_held(u <= step ? kv & ~TBIT : kv);
-                late &= u <= step ? ~(1u << e) : ~0u;
-                nexp = min(nexp, u <= step ? 0x7fffffff : u);
+            while (any) {
+                int el[4], u[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    el[k] = any ? __builtin_ctz(any) : EPT;
+                    any &= any - 1;
+                    u[k] = el[k] < EPT && (late >> el[k]) & 1u ? Tout[ro + el[k] * TB + tid] : 0x7fffffff;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (el[k] >= EPT) break;
+                    const uint32_t kv = Kb[el[k]];
+                    Kb[el[k]] = tabu_held(u[k] <= step ? kv & ~TBIT : kv);
+                    late &= u[k] <= step ? ~(1u << el[k]) : ~0u;
+                    nexp = min(nexp, u[k] <= step ? 0x7fffffff : u[k]);
+                }
             }
         }
         if ((int32_t)((uint64_t)gap >> 32) < 0) {
@@ -482,10 +503,21 @@ template <int EPT, typename QT, bool K32, int TB>
 qb_status launch_one(const QT *Qt, int ldp, qb_problem P, int z, uint8_t *X, int32_t *H, int64_t *E, int alpha,
                      int tenure, int asp, int32_t *T, int32_t *LF, uint32_t bias, hipStream_t s)
 {
-    const size_t lds = sizeof(int32_t) * 2 * (size_t)P->n;
+    // The ring holds the tenure's flips (a power of two of them, 1024 or
+    // more) as far as LDS has room: every tenure up to n below 15,600
+    // variables, 8191 beyond.  Past it each release is looked up: n = 7000,
+    // tenure 1024, 0.79 us a step with a ring of 2048 and 3.3 with 1024
+    // (n / 150: 0.73); n = 16384, tenure 5000, 0.90 and 2.8.
+    constexpr int LDS_MAX = 160 * 1024, fixed = 24 * TabuShape<TB>::NW + 4 * (TB + 4) + 64;   // static arrays
+    constexpr int flip = (int)sizeof(TabuFlip<TB>);
+    const int room = LDS_MAX - fixed - 8 * P->n;
+    int ring = 1024;
+    if (tenure < alpha)
+        while (ring <= tenure && 2 * ring * flip <= room) ring *= 2;
+    const int lds = 8 * P->n + ring * flip;
     QB_TRY_HIP(hipFuncSetAttribute((const void *)k_tabu<EPT, QT, K32, TB>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)lds));
-    k_tabu<EPT, QT, K32, TB><<<z, TB, lds, s>>>(Qt, ldp, P->Q, P->n, X, H, E, alpha, tenure, asp, T, LF, bias);
+                                   lds));
+    k_tabu<EPT, QT, K32, TB><<<z, TB, lds, s>>>(Qt, ldp, P->Q, P->n, X, H, E, alpha, tenure, asp, T, LF, bias, ring);
     QB_LAUNCH_CHECK();
     return QB_OK;
 }
@@ -498,7 +530,7 @@ qb_status launch_keyed(const QT *Qt, int ldp, qb_problem P, int z, uint8_t *X, i
     if (2 * dmax + 1 >= (int64_t)(0x7FFFFFFFu >> qb_ceil_log2(EPT))) return QB_E_RANGE;
     const uint32_t bias = (uint32_t)dmax;
     // one wave has no winners to compare, and int8 moves always fit
-    // (|D| <= 127 (2 n + 1): 2^23 for n = 16384)
+    // (2 dmax + 1 <= 254 (2 n + 1) + 1 < 2^23 for n = 16384)
     constexpr bool always = TB == 64 || (sizeof(QT) == 1 && TB < QB_TABU_THREADS);
     if (TB < QB_TABU_THREADS && ((2 * dmax + 1) << qb_ceil_log2(EPT)) < (int64_t(1) << (31 - TabuShape<TB>::WB)))
         return launch_one<EPT, QT, (TB < QB_TABU_THREADS), TB>(Qt, ldp, P, z, X, H, E, alpha, tenure, asp, T, LF, bias,

@@ -1,0 +1,75 @@
+"""Dense Tabu with long tenures: the ring of flips and the variables that are
+tabu past it, against the oracle, and their time."""
+import numpy as np
+import pytest
+
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _qubo(n, density, seed):
+    rng = np.random.default_rng(seed)
+    Q = rng.integers(-100, 101, (n, n), dtype=np.int16)
+    Q[rng.random((n, n), dtype=np.float32) >= density] = 0
+    Q = np.triu(Q)
+    return (Q + np.triu(Q, 1).T).astype(np.int16)
+
+
+# tenures of an odd ring, at both ends of n, past the last step (never
+# released) and one before it; n = 14000: too little LDS for the late
+# variables' steps; n = 16384: a tenure past the ring that fits LDS; n = 65:
+# nearly every flip a tabu one
+@pytest.mark.parametrize("n,tenure,alpha,asp", [
+    (65, 40, 3000, True), (65, 64, 900, False), (65, 300, 2000, True), (1000, 999, 4000, True),
+    (1000, 1100, 2500, False), (1537, 1500, 1501, True), (1537, 1501, 1501, True), (3000, 2999, 6500, True),
+    (9000, 1025, 3000, True), (14000, 4000, 7000, True), (16384, 15300, 16000, True)])
+def test_long_tenures_match_the_oracle(n, tenure, alpha, asp):
+    from paper_2502_13947_amd import qb
+    print("tenure", n, tenure, alpha, asp, flush=True)
+    Q = _qubo(n, 0.3, n + tenure)
+    rng = np.random.default_rng(n)
+    X = rng.integers(0, 2, (1, n)).astype(np.uint8)
+    P = qb.Problem(torch.as_tensor(Q, device="cuda"))
+    H = oracle.field(Q, X)
+    E = oracle.energy(X, H)
+    Xd, Hd, Ed = (torch.as_tensor(a, device="cuda") for a in (X, H, E))
+    T = torch.full((1, n), -7, dtype=torch.int32, device="cuda")
+    LF = torch.full((1, n), -7, dtype=torch.int32, device="cuda")
+    qb.tabu(P, Xd, Hd, Ed, alpha, tenure, asp, T, LF)
+    x, h, ov, To, LFo = oracle.tabu(Q, X[0], H[0], int(E[0]), alpha, tenure, asp)
+    assert (Xd[0].cpu().numpy() == x).all() and (Hd[0].cpu().numpy() == h).all()
+    assert int(Ed[0].item()) == ov
+    assert (T[0].cpu().numpy() == To).all() and (LF[0].cpu().numpy() == LFo).all()
+
+
+@pytest.mark.parametrize("n,tenure", [(7000, 1024), (7000, 2000), (7000, 3900), (1000, 1100), (1000, 3900)])
+def test_long_tenures_take_the_time_of_short_ones(n, tenure):
+    """A step's time does not depend on the tenure (it was two to four times
+    as long from 1024 on): at most 1.5 times that at n / 150."""
+    from paper_2502_13947_amd import qb
+    z, alpha = 64, 4000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    Q = torch.triu(torch.randint(-100, 101, (n, n), generator=g, device="cuda", dtype=torch.int16))
+    P = qb.Problem((Q + torch.triu(Q, 1).T).contiguous())
+    X = torch.randint(0, 2, (z, n), generator=g, device="cuda", dtype=torch.uint8)
+    H = torch.zeros((z, n), dtype=torch.int32, device="cuda")
+    E = torch.zeros(z, dtype=torch.int64, device="cuda")
+    T, LF = torch.zeros_like(H), torch.zeros_like(H)
+    qb.field(P, X, H)
+    qb.energy(X, H, E)
+    qb.tabu(P, X, H, E, n, n // 150, True, T, LF)
+    best = {}
+    for ten in (n // 150, tenure) * 4:
+        Xw, Hw, Ew = X.clone(), H.clone(), E.clone()
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        qb.tabu(P, Xw, Hw, Ew, alpha, ten, True, T, LF)
+        b.record()
+        torch.cuda.synchronize()
+        best[ten] = min(best.get(ten, 1e9), a.elapsed_time(b))
+    us = {t: 1e3 * v / alpha for t, v in best.items()}
+    print("n %d: %s us" % (n, "  ".join("tenure %d %.3f" % kv for kv in us.items())), flush=True)
+    assert us[tenure] <= 1.5 * us[n // 150]
