@@ -9,27 +9,18 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def _qubo(n, density, seed):
+def _qubo(n, density, seed, lim=100):
     rng = np.random.default_rng(seed)
-    Q = rng.integers(-100, 101, (n, n), dtype=np.int16)
+    Q = rng.integers(-lim, lim + 1, (n, n), dtype=np.int16)
     Q[rng.random((n, n), dtype=np.float32) >= density] = 0
     Q = np.triu(Q)
     return (Q + np.triu(Q, 1).T).astype(np.int16)
 
 
-# tenures of an odd ring, at both ends of n, past the last step (never
-# released) and one before it; n = 14000: too little LDS for the late
-# variables' steps; n = 16384: a tenure past the ring that fits LDS; n = 65:
-# nearly every flip a tabu one
-@pytest.mark.parametrize("n,tenure,alpha,asp", [
-    (65, 40, 3000, True), (65, 64, 900, False), (65, 300, 2000, True), (1000, 999, 4000, True),
-    (1000, 1100, 2500, False), (1537, 1500, 1501, True), (1537, 1501, 1501, True), (3000, 2999, 6500, True),
-    (9000, 1025, 3000, True), (14000, 4000, 7000, True), (16384, 15300, 16000, True)])
-def test_long_tenures_match_the_oracle(n, tenure, alpha, asp):
+def _check(Q, tenure, alpha, asp, seed):
     from paper_2502_13947_amd import qb
-    print("tenure", n, tenure, alpha, asp, flush=True)
-    Q = _qubo(n, 0.3, n + tenure)
-    rng = np.random.default_rng(n)
+    n = Q.shape[0]
+    rng = np.random.default_rng(seed)
     X = rng.integers(0, 2, (1, n)).astype(np.uint8)
     P = qb.Problem(torch.as_tensor(Q, device="cuda"))
     H = oracle.field(Q, X)
@@ -42,6 +33,35 @@ def test_long_tenures_match_the_oracle(n, tenure, alpha, asp):
     assert (Xd[0].cpu().numpy() == x).all() and (Hd[0].cpu().numpy() == h).all()
     assert int(Ed[0].item()) == ov
     assert (T[0].cpu().numpy() == To).all() and (LF[0].cpu().numpy() == LFo).all()
+
+
+# tenures of an odd ring, at both ends of n, past the last step (never
+# released) and one before it; n = 14000: too little LDS for the late
+# variables' steps; n = 16384: a tenure past the ring that fits LDS; n = 65:
+# nearly every flip a tabu one
+@pytest.mark.parametrize("n,tenure,alpha,asp", [
+    (65, 40, 3000, True), (65, 64, 900, False), (65, 300, 2000, True), (1000, 999, 4000, True),
+    (1000, 1100, 2500, False), (1537, 1500, 1501, True), (1537, 1501, 1501, True), (3000, 2999, 6500, True),
+    (9000, 1025, 3000, True), (14000, 4000, 7000, True), (16384, 15300, 16000, True)])
+def test_long_tenures_match_the_oracle(n, tenure, alpha, asp):
+    print("tenure", n, tenure, alpha, asp, flush=True)
+    _check(_qubo(n, 0.3, n + tenure), tenure, alpha, asp, n)
+
+
+# int16 weights whose move values leave no room for the wave's number in a
+# 32-bit key (between 2^29 or, with eight waves, 2^28, and 2^31 with the
+# element's bits), at an ordinary tenure and with every variable tabu
+@pytest.mark.parametrize("n,lim,tenure,alpha", [(2600, 9000, 17, 400), (2600, 9000, 5000, 2700), (6000, 5000, 40, 400),
+                                                (9000, 3000, 60, 400), (9000, 3000, 20000, 9100)])
+def test_wide_winners_match_the_oracle(n, lim, tenure, alpha):
+    print("wide winners", n, lim, tenure, alpha, flush=True)
+    Q = _qubo(n, 1.0, n + lim, lim)
+    waves = 4 if n <= 8192 else 8
+    per = -(-n // (64 * waves))
+    bits = (per if per % 4 == 0 else per + 2).bit_length()      # of the element
+    d = int(np.abs(Q.astype(np.int32)).max()) + 2 * int(np.abs(Q.astype(np.int64)).sum(axis=1).max())
+    assert (1 << (33 - waves.bit_length()) >> 1) <= (2 * d + 1) << bits < 1 << 31
+    _check(Q, tenure, alpha, True, n)
 
 
 @pytest.mark.parametrize("n,tenure", [(7000, 1024), (7000, 2000), (7000, 3900), (1000, 1100), (1000, 3900)])
