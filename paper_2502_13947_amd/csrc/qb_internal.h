@@ -413,7 +413,7 @@ __device__ __forceinline__ uint64_t qb_dpp_min64(uint64_t v)
 // (wave w's minimum key << log2 NW) | w and, in its high word,
 // (lane << 1) | x.  A 32-bit DPP minimum over the first row of lanes picks
 // the winning key and one readlane of that slot's high word gives its lane
-// and x.  False when every slot is empty.
+// and x.  False (key all ones) when every slot is empty.
 template <int NWV>
 __device__ __forceinline__ bool qb_pick32(const uint64_t *slot, int lane, uint32_t &key, uint32_t &hi)
 {
@@ -431,9 +431,8 @@ __device__ __forceinline__ bool qb_pick32(const uint64_t *slot, int lane, uint32
     if constexpr (NWV > 8)
         lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x128, 0xF, 0xF, false));  // row_ror 8
     key = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
-    if (key == 0xFFFFFFFFu) return false;
     hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)(key & (NWV - 1)));
-    return true;
+    return key != 0xFFFFFFFFu;
 }
 
 // Minimum of NW (<= 16) 64-bit values slot[0..NW), returned uniform: lane l

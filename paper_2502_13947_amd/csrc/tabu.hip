@@ -117,26 +117,6 @@ struct TabuRow {
     }
 };
 
-// The winning slot of NWV (wave minimum << WB | wave in the low word, the
-// wave's mark in the high one), uniform; all ones when every slot is empty.
-template <int NWV>
-__device__ __forceinline__ void tabu_pick32(const uint64_t *slot, int lane, uint32_t &key, uint32_t &hi)
-{
-    static_assert(NWV <= 16, "one row of 16 lanes");
-    // every lane reads a slot (lanes past NWV repeat them): no exec mask
-    const uint64_t v = slot[lane & (NWV - 1)];
-    uint32_t lo = (uint32_t)v;
-    lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
-    lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
-    // eight slots: the upper half of the row repeats the lower
-    if constexpr (NWV > 4)
-        lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x124, 0xF, 0xF, false));  // row_ror 4
-    if constexpr (NWV > 8)
-        lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x128, 0xF, 0xF, false));  // row_ror 8
-    key = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
-    hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), (int)(key & (NWV - 1)));
-}
-
 // The words of a row are not looked at before this point.
 template <int N>
 __device__ __forceinline__ void tabu_arrive(uint32_t (&w)[N])
@@ -303,15 +283,14 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
             qb_lds_barrier();
             if constexpr (K32) {
                 uint32_t key, hi;
-                tabu_pick32<NW>(slots, lane, key, hi);
-                if (__builtin_expect(key == ~0u, 0)) {
+                if (__builtin_expect(!qb_pick32<NW>(slots, lane, key, hi), 0)) {
                     // every variable is tabu and none aspirates: argmin over all of them
                     const uint32_t b2 = min(fk, tk);
                     const uint32_t w2 = qb_wave_min_u32_b(b2);
                     const uint64_t k2 = slot_of(w2, b2, mark_of(b2));
                     if (lane == 0) red2[wid] = k2;
                     qb_lds_barrier();
-                    tabu_pick32<NW>(red2, lane, key, hi);
+                    qb_pick32<NW>(red2, lane, key, hi);
                 }
                 const uint32_t wm = key >> WB;
                 dib = wm >> EB;
