@@ -75,6 +75,49 @@ __global__ void k_random_keys(int n, int t, const qb_iter *__restrict__ it, uint
         if (4 * g + w < n) row[4 * g + w] = (int64_t)qb_word(o, w);
 }
 
+// Element j as one key, ascending in (K desc, index asc).  Keys are within
+// +-lim by construction; the clamp only keeps the index bits intact if a
+// caller breaks that contract.
+__device__ __forceinline__ uint64_t rank_key(const int64_t *__restrict__ Kp, int j)
+{
+    constexpr int64_t lim = (int64_t(1) << 47) - 1;
+    const int64_t k = min(max(Kp[j], -lim), lim);
+    return ((uint64_t)(lim - k) << 16) | (uint64_t)j;
+}
+
+// Rank for n <= 1024: bitonic sort of (K desc, index asc) packed into one
+// 64-bit key per element, a thread per comparison.  Its few stages take less
+// than the passes of the radix sort below, whose counters have to be cleared
+// and summed whatever n is (47-bit keys: 1024 solutions of n = 64 6.6 us
+// against 42, of n = 1000 22.5 against 44; n = 1500, 16 solutions, whose
+// network has 2048 elements, 21.1 us against 17.4).
+constexpr int RANK_SMALL = 1024;
+
+__global__ void __launch_bounds__(RANK_SMALL / 2) k_rank_small(int n, int npad, const int64_t *__restrict__ K,
+                                                               int32_t *__restrict__ order)
+{
+    __shared__ uint64_t sk[RANK_SMALL];
+    const int p = blockIdx.x, nt = blockDim.x;
+    const int64_t *Kp = K + (int64_t)p * n;
+    for (int i = threadIdx.x; i < npad; i += nt) sk[i] = i < n ? rank_key(Kp, i) : ~0ull;
+    __syncthreads();
+    for (int k = 2; k <= npad; k <<= 1) {
+        for (int jj = k >> 1; jj > 0; jj >>= 1) {
+            const int i = threadIdx.x;
+            if (i < npad >> 1) {
+                const int lo = ((i & ~(jj - 1)) << 1) | (i & (jj - 1)), hi = lo + jj;
+                const uint64_t a = sk[lo], b = sk[hi];
+                if ((a > b) == ((lo & k) == 0)) {
+                    sk[lo] = b;
+                    sk[hi] = a;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    for (int r = threadIdx.x; r < n; r += nt) order[(int64_t)p * n + r] = (int32_t)(sk[r] & 0xffffu);
+}
+
 // Rank for n <= 32768: a stable radix sort of one solution per workgroup, 8
 // bits a pass over the bits in which its keys differ (max K - K, so that the
 // order is K descending; equal keys keep their index order).  Element e is
@@ -89,6 +132,9 @@ __global__ void k_random_keys(int n, int t, const qb_iter *__restrict__ it, uint
 // barriers.  n = 7000, 256 solutions, 32-bit keys: 28 us, against 80 us
 // with a bitonic network in LDS; n = 20000, 16 solutions, keys of up to 47 bits: 45 us,
 // against 323 us with that network on chunks.
+// n is rounded up to 1024 V elements, which a pass costs: V steps by at most a
+// factor of two, and 7 and 20 lie just above n = 7000 and 20000.  Above 20 the elements no longer all fit the registers (n = 25000 and
+// 32768, 16 solutions: 141 and 143 us, against 341 and 378 on chunks).
 constexpr int RANK_WAVES = 16, RANK_MAX_V = 32;
 
 template <int V>
@@ -230,13 +276,6 @@ qb_status launch_rank(int n, int z, const int64_t *K, int32_t *order, hipStream_
 // the indices in global memory (one workgroup per solution, so a barrier
 // orders them).
 constexpr int RANK_CHUNK = 16384;
-
-__device__ __forceinline__ uint64_t rank_key(const int64_t *__restrict__ Kp, int j)
-{
-    constexpr int64_t lim = (int64_t(1) << 47) - 1;
-    const int64_t k = min(max(Kp[j], -lim), lim);
-    return ((uint64_t)(lim - k) << 16) | (uint64_t)j;
-}
 
 __device__ __forceinline__ void bitonic_positions(int i, int k, int jj, bool flip, int &lo, int &hi)
 {
@@ -516,8 +555,14 @@ extern "C" qb_status qb_rank(int32_t n, int32_t z, const int64_t *K_d, int32_t *
 {
     if (n < 1 || n > 65535 || z < 1 || !K_d || !order_d) return QB_E_ARG;
     hipStream_t s = qb_stream(stream);
+    if (n <= RANK_SMALL) {
+        int npad = 2;
+        while (npad < n) npad <<= 1;
+        k_rank_small<<<z, std::max(npad / 2, 64), 0, s>>>(n, npad, K_d, order_d);
+        QB_LAUNCH_CHECK();
+        return QB_OK;
+    }
     const int v = (n + 1023) / 1024;
-    if (v <= 1) return launch_rank<1>(n, z, K_d, order_d, s);
     if (v <= 2) return launch_rank<2>(n, z, K_d, order_d, s);
     if (v <= 4) return launch_rank<4>(n, z, K_d, order_d, s);
     if (v <= 7) return launch_rank<7>(n, z, K_d, order_d, s);

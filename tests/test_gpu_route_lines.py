@@ -99,3 +99,24 @@ def test_plan_kernel_without_the_class_is_the_automatic_one(lim, m, kernel):
     """A plan that names a kernel which cannot run the class."""
     named, auto = two_plans(lim, m, 64, 1, 200, (kernel, 0))
     assert named <= 1.6 * auto
+
+
+def rank_ms(n, z):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    K = torch.randint(-2**46, 2**46, (z, n), generator=g, device=DEV, dtype=torch.int64)
+    K[:, ::3] = K[:, :1].clone()                             # ties
+    order = torch.full((z, n), -1, dtype=torch.int32, device=DEV)
+    ms = best_ms(lambda: qb().rank(K, order), 20)
+    want = torch.argsort(K, dim=1, descending=True, stable=True).to(torch.int32)
+    assert torch.equal(order, want), n
+    return ms
+
+
+def test_small_ranks_are_cheap():
+    """Ranking few variables takes less than ranking a thousand (it took the
+    same, three to six times as long as it has to)."""
+    ms = {n: rank_ms(n, 2048) for n in (1, 2, 3, 63, 64, 65, 128, 200, 513, 1000, 1023, 1024, 1025)}
+    print("rank: " + "  ".join(f"n {n} {v:.4f}" for n, v in ms.items()) + " ms", flush=True)
+    assert max(ms[n] for n in (1, 2, 3, 63, 64, 65)) <= 0.5 * ms[1000]
+    assert ms[1000] <= 1.2 * ms[1025]
