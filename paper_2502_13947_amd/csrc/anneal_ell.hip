@@ -16,6 +16,8 @@
 // once, the lowest accepting lane taken by ballot and find-first-set, lanes
 // past it re-evaluated after its row was added), and serves the jobs that do
 // not leave LDS for the other's tables, and rows wider than 255.
+#include <algorithm>
+
 #include "qb_internal.h"
 
 namespace {
@@ -25,10 +27,10 @@ constexpr int DBLK_BYTES = 64 * 64;   // one diagonal block, int8
 // ------------------------------------------------------------------ extract
 // One workgroup per job, one thread per row: the entries of Q's row S_a whose
 // column is in S become the row's ELL words with local column indices; c and
-// F0 as in the dense extraction.  A variable's place in S is looked up in an
-// LDS table over all n variables, and rows are read and written 16 bytes at a
-// time (n = 20000, 128 jobs of 1024: 13 us; 102 us with a binary search
-// per entry, single words and 256 threads).
+// F0 as in the dense extraction.  Rows are read and written 16 bytes at a
+// time.  TABLE: a variable's place in S is looked up in an LDS table over all
+// n variables, else searched for in S (qb_extract_ell says when).
+template <bool TABLE>
 __global__ void __launch_bounds__(1024) k_extract_ell(const uint32_t *__restrict__ ell, int W,
                                                       const int32_t *__restrict__ ecnt,
                                                       const int32_t *__restrict__ diag, int n,
@@ -41,28 +43,51 @@ __global__ void __launch_bounds__(1024) k_extract_ell(const uint32_t *__restrict
                                                       uint8_t *__restrict__ y0, uint8_t *__restrict__ dblk,
                                                       const int32_t *__restrict__ dboff)
 {
-    extern __shared__ __align__(16) uint16_t place[];   // [n] 1 + place in S, with x in bit 15; 0 outside
-    const int q = blockIdx.x, tid = threadIdx.x;
+    // TABLE: [n] 1 + place in S, with x in bit 15; 0 outside.  Else [m]
+    // twice the variable plus x, ascending
+    extern __shared__ __align__(16) uint32_t lds[];
+    uint16_t *place = reinterpret_cast<uint16_t *>(lds);
+    const int q = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
     const int base = off[q], m = off[q + 1] - base, p = sol[q];
     const int64_t xo = (int64_t)p * n;
-    for (int t = tid; t < (n + 7) / 8; t += 1024) reinterpret_cast<uint4 *>(place)[t] = make_uint4(0, 0, 0, 0);
+    if constexpr (TABLE) {
+        for (int t = tid; t < (n + 7) / 8; t += nt) reinterpret_cast<uint4 *>(place)[t] = make_uint4(0, 0, 0, 0);
+    }
     // the job's diagonal 64 x 64 blocks (int8), zeroed before the rows fill them
     uint8_t *dq = dblk ? dblk + (size_t)dboff[q] * DBLK_BYTES : nullptr;
     if (dq) {
         const int n16 = qb_tile_ms(m) * DBLK_BYTES / 16;
-        for (int t = tid; t < n16; t += 1024) reinterpret_cast<uint4 *>(dq)[t] = make_uint4(0, 0, 0, 0);
+        for (int t = tid; t < n16; t += nt) reinterpret_cast<uint4 *>(dq)[t] = make_uint4(0, 0, 0, 0);
     }
-    __syncthreads();
-    const int a = tid;                                   // m <= 1024: a row per thread
+    if constexpr (TABLE) __syncthreads();
+    const int a = tid;                                   // m <= the workgroup's threads: a row per thread
     int i = 0;
     int32_t y = 0;
     if (a < m) {
         i = idx[base + a];
         y = X[xo + i];
-        place[i] = (uint16_t)(1 + a + (y ? 0x8000 : 0));
+        if constexpr (TABLE)
+            place[i] = (uint16_t)(1 + a + (y ? 0x8000 : 0));
+        else
+            lds[a] = 2u * (uint32_t)i + (y ? 1u : 0u);
     }
     __syncthreads();
     if (a >= m) return;
+    // 1 + place in S, with x in bit 15, of a variable; 0 outside
+    auto find = [&](int j) -> uint32_t {
+        if constexpr (TABLE) {
+            return place[j];
+        } else {
+            int lo = 0;                                  // the last place whose variable is at most j
+            for (int h = m; h > 1;) {
+                const int half = h >> 1;
+                lo = lds[lo + half] < 2u * (uint32_t)j + 2u ? lo + half : lo;
+                h -= half;
+            }
+            const uint32_t v = lds[lo];
+            return v >> 1 == (uint32_t)j ? 1u + (uint32_t)lo + ((v & 1u) << 15) : 0u;
+        }
+    };
     const int32_t qii = diag[i];
     const int32_t f0 = qii + 2 * (H[xo + i] - qii * y);
     F0[base + a] = f0;
@@ -79,7 +104,7 @@ __global__ void __launch_bounds__(1024) k_extract_ell(const uint32_t *__restrict
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (t + u >= cnt) break;
-            const uint32_t pl = place[qb_ell_col(wv[u])];
+            const uint32_t pl = find(qb_ell_col(wv[u]));
             if (pl == 0u) continue;
             const int32_t v = qb_ell_val(wv[u]);
             const int pos = (int)(pl & 0x7fffu) - 1;
@@ -536,10 +561,22 @@ extern "C" qb_status qb_extract_ell(qb_problem P, qb_batch b, const uint8_t *X_d
     if (b->J == 0) return QB_OK;
     // int8 problems also get the jobs' diagonal blocks (for the annealer's register path)
     uint8_t *dblk = P->int8_ok ? reinterpret_cast<uint8_t *>(tile_d + (int64_t)b->total * P->ellw) : nullptr;
-    const int lds = (P->n + 7) / 8 * 16;
-    QB_TRY_HIP(hipFuncSetAttribute((const void *)k_extract_ell, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-    k_extract_ell<<<b->J, 1024, lds, qb_stream(stream)>>>(P->ell, P->ellw, P->ecnt, P->diag, P->n, b->sol_d, b->off_d,
-                                                          b->idx_d, X_d, H_d, tile_d, c_d, F0_d, y0_d, dblk, b->dboff_d);
+    // The table, unless clearing it for every job costs more than searching:
+    // many jobs a compute unit, of few variables and entries beside n.  20000
+    // variables, rows of 40: 16384 jobs of 10 take 120 us with it and 48
+    // without, of 64 160 and 120, of 128 267 and 293; 2048 jobs of 64 25 and
+    // 32.  Rows of 8: 16384 jobs of 64 74 and 39, of 128 82 and 68; 247 of
+    // 1024 11 and 16.  The workgroup has a row per thread, and for the table
+    // at least 8 threads per KB of it.
+    int ncu = 0;
+    QB_TRY_HIP(qb_cu_count(&ncu));
+    const bool table = (int64_t)b->J * P->n <= (int64_t)240000 * ncu || P->n <= (int64_t)b->m_max * (128 + 4 * P->ellw);
+    const int nt = (std::min(std::max(b->m_max, table ? P->n / 64 : 0), 1024) + 63) / 64 * 64;
+    const int lds = table ? (P->n + 7) / 8 * 16 : 4 * b->m_max;
+    const auto kern = table ? k_extract_ell<true> : k_extract_ell<false>;
+    QB_TRY_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    kern<<<b->J, nt, lds, qb_stream(stream)>>>(P->ell, P->ellw, P->ecnt, P->diag, P->n, b->sol_d, b->off_d, b->idx_d,
+                                               X_d, H_d, tile_d, c_d, F0_d, y0_d, dblk, b->dboff_d);
     QB_LAUNCH_CHECK();
     return QB_OK;
 }

@@ -120,3 +120,64 @@ def test_small_ranks_are_cheap():
     print("rank: " + "  ".join(f"n {n} {v:.4f}" for n, v in ms.items()) + " ms", flush=True)
     assert max(ms[n] for n in (1, 2, 3, 63, 64, 65)) <= 0.5 * ms[1000]
     assert ms[1000] <= 1.2 * ms[1025]
+
+
+def ell_jobs(n, z, k, m, W, seed):
+    """z solutions of k jobs of m random variables on a circulant graph with W
+    entries a row: the outputs of qb_extract_ell and its time."""
+    i = np.repeat(np.arange(n), W)
+    j = (i + np.tile(np.concatenate([np.arange(1, W // 2 + 1), -np.arange(1, W // 2 + 1)]), n)) % n
+    o = np.lexsort((j, i))
+    v = ((np.minimum(i, j) * 7919 + np.maximum(i, j) * 104729) % 11 - 5)[o]
+    v[v == 0] = 6
+    P = qb().Problem.from_csr((np.arange(n + 1) * W).astype(np.int32), j[o].astype(np.int32), v.astype(np.int16), DEV)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    X = torch.randint(0, 2, (z, n), generator=g, device=DEV, dtype=torch.uint8)
+    H = torch.zeros((z, n), dtype=torch.int32, device=DEV)
+    qb().field(P, X, H)
+    order = torch.argsort(torch.rand((z, n), generator=g, device=DEV), dim=1).to(torch.int32).contiguous()
+    b = qb().Batch(n, z, np.repeat(np.arange(z), k), np.full(z * k, m))
+    qb().select(b, order)
+    tile = torch.full((qb().ell_tile_words(b, P.ell_width),), -1, dtype=torch.int32, device=DEV)
+    F0 = torch.zeros(b.total, dtype=torch.int32, device=DEV)
+    y0 = torch.zeros(b.total, dtype=torch.uint8, device=DEV)
+    c = torch.zeros(b.total, dtype=torch.int32, device=DEV)
+    ms = best_ms(lambda: qb().extract_ell(P, b, X, H, tile, F0, y0, c))
+    return P, b, X, H, tile, F0, y0, c, ms
+
+
+# both ways of finding a column's place (a table over all variables; a search
+# in the job's index set), with jobs of one variable, odd sizes and the largest
+@pytest.mark.parametrize("n,z,k,m,W", [(5000, 64, 260, 1, 8), (5000, 64, 260, 17, 8), (20001, 64, 256, 33, 10),
+                                       (40000, 40, 128, 100, 6), (1000, 4, 3, 33, 8), (65535, 8, 40, 33, 4),
+                                       (3001, 2, 2, 1024, 12)])
+def test_extract_ell_finds_places_both_ways(n, z, k, m, W):
+    """Rows, c, F0 and y0 of a sample of the jobs, rebuilt from the circulant
+    rows."""
+    P, b, X, H, tile, F0, y0, c, _ = ell_jobs(n, z, k, m, W, n)
+    idx = b.idx(DEV).cpu().numpy()
+    Xh, Hh = X.cpu().numpy(), H.cpu().numpy()
+    Fh, yh, ch = F0.cpu().numpy(), y0.cpu().numpy(), c.cpu().numpy()
+    step = np.concatenate([np.arange(1, W // 2 + 1), -np.arange(1, W // 2 + 1)])
+    for q in range(0, b.J, max(1, b.J // 50)):
+        p, sl = q // k, slice(q * m, (q + 1) * m)
+        S = idx[sl]
+        I, J = np.repeat(S, W), (np.repeat(S, W) + np.tile(step, m)) % n
+        v = (np.minimum(I, J) * 7919 + np.maximum(I, J) * 104729) % 11 - 5
+        v[v == 0] = 6
+        at = np.searchsorted(S, J)
+        hit = (at < m) & (S[np.minimum(at, m - 1)] == J)
+        T = np.zeros((m, m), np.int64)
+        T[np.repeat(np.arange(m), W)[hit], at[hit]] = v[hit]
+        assert (qb().untile_ell(tile, b, q, P.ell_width) == T).all(), q
+        assert (yh[sl] == Xh[p, S]).all() and (Fh[sl] == 2 * Hh[p, S]).all(), q
+        assert (ch[sl] == 2 * Hh[p, S] - 2 * T @ Xh[p, S].astype(np.int64)).all(), q
+
+
+def test_small_sparse_jobs_of_many_variables():
+    """Extracting many small jobs does not depend on n (it took five times as
+    long at n = 65535)."""
+    ms = {n: ell_jobs(n, 64, 256, 16, 8, 1)[-1] for n in (5000, 65535)}
+    print("extract: " + "  ".join(f"n {n} {v:.4f}" for n, v in ms.items()) + " ms", flush=True)
+    assert ms[65535] <= 1.7 * ms[5000]
