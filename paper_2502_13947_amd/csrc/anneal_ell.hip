@@ -551,16 +551,16 @@ qb_status dispatch_ell(int cls, int njobs, int rw, int R, hipStream_t s, const i
 
 }  // namespace
 
-extern "C" qb_status qb_extract_ell(qb_problem P, qb_batch b, const uint8_t *X_d, const int32_t *H_d,
-                                   uint32_t *tile_d, int32_t *c_d, int32_t *F0_d, uint8_t *y0_d, void *stream)
+// `blocks`: also the int8 diagonal blocks, which no kernel reads.
+qb_status qb_extract_ell_x(qb_problem P, qb_batch b, const uint8_t *X_d, const int32_t *H_d, uint32_t *tile_d,
+                           int32_t *c_d, int32_t *F0_d, uint8_t *y0_d, bool blocks, void *stream)
 {
     if (!P || !b || !X_d || !H_d || !tile_d || !F0_d || !y0_d) return QB_E_ARG;
     if (b->n != P->n) return QB_E_ARG;
     if (!P->sparse) return QB_E_UNSUPPORTED;
     if ((uintptr_t)tile_d & 15) return QB_E_ARG;
     if (b->J == 0) return QB_OK;
-    // int8 problems also get the jobs' diagonal blocks (for the annealer's register path)
-    uint8_t *dblk = P->int8_ok ? reinterpret_cast<uint8_t *>(tile_d + (int64_t)b->total * P->ellw) : nullptr;
+    uint8_t *dblk = blocks && P->int8_ok ? reinterpret_cast<uint8_t *>(tile_d + (int64_t)b->total * P->ellw) : nullptr;
     // The table, unless clearing it for every job costs more than searching:
     // many jobs a compute unit, of few variables and entries beside n.  20000
     // variables, rows of 40: 16384 jobs of 10 take 120 us with it and 48
@@ -579,6 +579,12 @@ extern "C" qb_status qb_extract_ell(qb_problem P, qb_batch b, const uint8_t *X_d
                                                X_d, H_d, tile_d, c_d, F0_d, y0_d, dblk, b->dboff_d);
     QB_LAUNCH_CHECK();
     return QB_OK;
+}
+
+extern "C" qb_status qb_extract_ell(qb_problem P, qb_batch b, const uint8_t *X_d, const int32_t *H_d,
+                                   uint32_t *tile_d, int32_t *c_d, int32_t *F0_d, uint8_t *y0_d, void *stream)
+{
+    return qb_extract_ell_x(P, b, X_d, H_d, tile_d, c_d, F0_d, y0_d, true, stream);
 }
 
 qb_status qb_anneal_ell_x(qb_batch b, int32_t W, const uint32_t *tile_d, const int32_t *F0_d, const uint8_t *y0_d,

@@ -185,6 +185,8 @@ struct qb_iter {
 qb_status qb_anneal_x(qb_batch b, const void *tile_d, int32_t int8_tile, const int32_t *F0_d, const uint8_t *y0_d,
                       int32_t nsw, int32_t B, const int32_t *thr_d, int32_t R, uint64_t seed, uint32_t inst_base,
                       const qb_iter *it, uint8_t *Y_d, int64_t *e_d, void *stream);
+qb_status qb_extract_ell_x(qb_problem P, qb_batch b, const uint8_t *X_d, const int32_t *H_d, uint32_t *tile_d,
+                           int32_t *c_d, int32_t *F0_d, uint8_t *y0_d, bool blocks, void *stream);
 qb_status qb_anneal_ell_x(qb_batch b, int32_t W, const uint32_t *tile_d, const int32_t *F0_d, const uint8_t *y0_d,
                           int32_t nsw, int32_t B, const int32_t *thr_d, int32_t R, int32_t rw, uint64_t seed,
                           uint32_t inst_base, const qb_iter *it, uint8_t *Y_d, int64_t *e_d, void *stream);

@@ -105,7 +105,7 @@ bool use(qb_state S, T **dst, T *given, size_t count)
 qb_status st_extract(qb_state S, qb_batch b, void *tiles, int32_t *F0, uint8_t *y0, hipStream_t s)
 {
     if (S->P->sparse)
-        return qb_extract_ell(S->P, b, S->b.X, S->b.H, (uint32_t *)tiles, nullptr, F0, y0, s);
+        return qb_extract_ell_x(S->P, b, S->b.X, S->b.H, (uint32_t *)tiles, nullptr, F0, y0, false, s);
     return qb_extract(S->P, b, S->b.X, S->b.H, tiles, nullptr, F0, y0, s);
 }
 
@@ -285,7 +285,7 @@ extern "C" qb_status qb_state_create(qb_state *out, qb_problem P, const qb_run_c
     }
     const qb_batch b = S->batch;
     auto tile_bytes = [&](qb_batch bb) -> size_t {
-        if (P->sparse) return sizeof(uint32_t) * ((size_t)bb->total * P->ellw + (size_t)bb->dblk_words);
+        if (P->sparse) return sizeof(uint32_t) * (size_t)bb->total * P->ellw;
         return (size_t)bb->tile_elems * S->tile_esz;
     };
     const size_t zn = (size_t)z * n;
