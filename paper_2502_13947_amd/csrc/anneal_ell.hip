@@ -10,12 +10,6 @@
 // accepted row's entries are added there by LDS atomic adds.  The job's ELL
 // tile is staged in LDS once and shared by the rw replicas (waves) of the
 // workgroup; rw only changes the schedule.
-//
-// k_anneal_ell_spec decides a whole sweep at once and repairs it;
-// k_anneal_ell takes accepts one by one (a block's 64 candidates evaluated at
-// once, the lowest accepting lane taken by ballot and find-first-set, lanes
-// past it re-evaluated after its row was added), and serves the jobs that do
-// not leave LDS for the other's tables, and rows wider than 255.
 #include <algorithm>
 
 #include "qb_internal.h"
@@ -134,164 +128,58 @@ __global__ void __launch_bounds__(1024) k_extract_ell(const uint32_t *__restrict
 }
 
 // ------------------------------------------------------------------ anneal
-template <int MS>
-__global__ void __launch_bounds__(1024) k_anneal_ell(const int32_t *__restrict__ jobs, int rgroups,
-                                                     const int32_t *__restrict__ off, int W,
-                                                     const uint32_t *__restrict__ tiles,
-                                                     const int32_t *__restrict__ F0,
-                                                     const uint8_t *__restrict__ y0, int nsw, int B,
-                                                     const int32_t *__restrict__ thr, int R, int rw, uint32_t k0,
-                                                     uint32_t k1, uint32_t inst_base, const qb_iter *__restrict__ it, uint8_t *__restrict__ Y,
-                                                     int64_t *__restrict__ eout, int32_t *__restrict__ acnt)
-{
-    constexpr int MP = 64 * MS;
-    extern __shared__ __align__(16) uint32_t dl[];
-    const int q = jobs[blockIdx.x / rgroups];
-    const int rg = blockIdx.x % rgroups;
-    const int base = off[q], m = off[q + 1] - base;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int r = rg * rw + wid;
-
-    uint32_t *tl = dl;                                   // [m][W]
-    int32_t *F = reinterpret_cast<int32_t *>(dl + (size_t)MP * W) + wid * MP;
-    {
-        const uint4 *src = reinterpret_cast<const uint4 *>(tiles + (int64_t)base * W);
-        uint4 *dst = reinterpret_cast<uint4 *>(tl);
-        const int n16 = m * W / 4;
-        for (int t = tid; t < n16; t += blockDim.x) dst[t] = src[t];
-    }
-#pragma unroll
-    for (int s = 0; s < MS; ++s) {
-        const int pos = 64 * s + lane;
-        F[pos] = pos < m ? F0[base + pos] : 0;
-    }
-    __syncthreads();
-    if (r >= R) return;   // no barrier follows
-
-    uint32_t ybits = 0;
-    uint64_t active[MS];
-#pragma unroll
-    for (int s = 0; s < MS; ++s) {
-        const int pos = 64 * s + lane;
-        if (pos < m && y0[base + pos]) ybits |= 1u << s;
-        const int na = min(max(m - 64 * s, 0), 64);
-        active[s] = na == 64 ? ~0ull : ((1ull << na) - 1ull);
-    }
-    int64_t e = 0;
-    int32_t nacc = 0;
-    const uint32_t tag = (1u << 28) | (inst_base + (it ? it->inst : 0u) + (uint32_t)q);
-    constexpr int G = (MS + 3) / 4;
-    const int sh = 32 - B;
-
-    for (int sw = 0; sw < nsw; ++sw) {
-        uint32_t u[4 * G];
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const uint4 o = qb_philox(make_uint4(((uint32_t)g << 6) | (uint32_t)lane, (uint32_t)sw, (uint32_t)r, tag),
-                                      k0, k1);
-            u[4 * g + 0] = o.x;
-            u[4 * g + 1] = o.y;
-            u[4 * g + 2] = o.z;
-            u[4 * g + 3] = o.w;
-        }
-        const int32_t *ts = thr + ((size_t)sw << B);
-        int32_t tv[MS];
-#pragma unroll
-        for (int s = 0; s < MS; ++s) tv[s] = ts[u[s] >> sh];
-#pragma unroll
-        for (int s = 0; s < MS; ++s) {
-            uint64_t pend = active[s];
-            if (pend == 0) continue;
-            int32_t fs = F[64 * s + lane];
-            // the first 64 words of the row of lane kp, read one accept ahead:
-            // kp is the next accepting lane of the current ballot, which is
-            // most often the next accept, and its row read then overlaps the
-            // current update instead of following it
-            int kp = -1;
-            uint32_t wp = 0u;
-            while (true) {
-                const uint32_t yb = (ybits >> s) & 1u;
-                const int32_t dE = yb ? -fs : fs;
-                const uint64_t acc = __ballot(dE <= tv[s]) & pend;
-                if (acc == 0) break;
-                const int k = __builtin_ctzll(acc);
-                const int32_t dEk = __builtin_amdgcn_readlane(dE, k);
-                const int32_t ykb = __builtin_amdgcn_readlane((int32_t)yb, k);
-                e += dEk;
-                ++nacc;
-                const int32_t d2 = ykb ? -2 : 2;
-                if (lane == k) ybits ^= 1u << s;
-                const uint32_t *row = tl + (size_t)(64 * s + k) * W;
-                // (word lane of a row is inside the LDS allocation for every
-                // lane: the fields of the replicas follow the tile)
-                uint32_t w0 = wp;
-                if (kp != k) w0 = row[lane];
-                if (lane < W && w0 != 0u) atomicAdd(&F[qb_ell_col(w0)], d2 * qb_ell_val(w0));
-                for (int t0 = 64; t0 < W; t0 += 64) {
-                    if (t0 + lane < W) {
-                        const uint32_t wd = row[t0 + lane];
-                        if (wd != 0u) atomicAdd(&F[qb_ell_col(wd)], d2 * qb_ell_val(wd));
-                    }
-                }
-                // issued after the adds (which return nothing), so only the
-                // read of the fields below waits for it
-                const uint64_t rest = acc & ~((2ull << k) - 1ull);
-                kp = rest ? __builtin_ctzll(rest) : -1;
-                if (kp >= 0) wp = tl[(size_t)(64 * s + kp) * W + lane];
-                pend &= ~((2ull << k) - 1ull);
-                fs = F[64 * s + lane];
-            }
-        }
-    }
-
-    uint8_t *Yr = Y + (size_t)base * R + (size_t)r * m;
-#pragma unroll
-    for (int s = 0; s < MS; ++s) {
-        const int pos = 64 * s + lane;
-        if (pos < m) Yr[pos] = (uint8_t)((ybits >> s) & 1u);
-    }
-    if (lane == 0) eout[(size_t)q * R + r] = e;
-    if (acnt && lane == 0) acnt[(size_t)q * R + r] = nacc;
-}
-
-// The same sweep, speculated: a whole sweep is decided at once and repaired
-// until it agrees with the sequential one (the fixed point of evaluating
-// every position against a guess of all decisions is the sequential sweep's,
-// as a position's answer depends on lower positions only).  A row of a sparse
-// tile reaches few positions, so almost every first guess is right: on the
-// sub-QUBOs of the n = 20000 workload (1024 variables, 230 accepts a sweep)
-// 2.8 rounds change anything, against a chain of 230 accepts.
+// One wave per replica, lane L holding the positions 64 s + L; F lives in LDS.
+// A sweep goes one of two ways, both exact, chosen by the positions that would
+// accept at its start.
 //
-// One wave per replica, lane L holding the positions 64 s + L.  F lives in
-// LDS.  A round compares every position's field with its threshold and adds
-// what the changed decisions make of the fields of *later* positions (LDS
+// Many: the whole sweep is decided at once and repaired until it agrees with
+// the sequential one (the fixed point of evaluating every position against a
+// guess of all decisions is the sequential sweep's, as a position's answer
+// depends on lower positions only).  A row of a sparse tile reaches few
+// positions, so almost every first guess is right: on the sub-QUBOs of the
+// n = 20000 workload (1024 variables, 230 accepts a sweep) 2.8 rounds change
+// anything.  A round compares every position's field with its threshold and
+// adds what the changed decisions make of the fields of *later* positions (LDS
 // atomic adds); once nothing changes, the accepted rows' entries at earlier
 // positions are added too.  Entries ascend by column, so a row's earlier part
 // comes first; of either part the first entry is in registers, and the others
-// are read from the tile in LDS by the few lanes that have any.  With F exact
-// at both ends the energy of the whole run is 1/2 sum (y - y0) (F0 + F): no
-// sweep sums it.  The thresholds of KT sweeps at a time are staged in LDS (KT
-// = 0: read from memory), one barrier per KT sweeps.
+// are read from the tile in LDS by the few lanes that have any.
 //
-// Bound by a wave's own instructions and LDS round trips (12,000 cycles a
-// sweep of 1024, Philox 2200 of them; 16 replicas take as long as one).
-// Measured, 128 jobs x 16 replicas x 1000 sweeps: 5.1 ms, against 30.2 ms for
-// a kernel that chained the accepts one by one with the block's couplings in
-// registers.
+// Few: one accept after another, a block of 64 positions at a time: the lowest
+// accepting lane by ballot and find-first-set, its whole row added by all
+// lanes, the block's fields read again.  A chain of accepts, but rows of any
+// length cost the same, where the way above walks them entry by entry on a
+// lane, in every round.
+//
+// The line between the two, `few`, lies where both took the same time at m =
+// 64 to 1024 and d = 4 to 30 entries a row within the job: MS (0.1 + d / 40) +
+// d / 2 + d^2 / 10 accepts, as lanes that hold one.
+//
+// With F exact at both ends of a sweep the energy of the whole run is
+// 1/2 sum (y - y0) (F0 + F): no sweep sums it.  A sweep's thresholds are read
+// from memory during the one before.
+//
+// Bound by a wave's own instructions and LDS round trips (16 replicas take as
+// long as one).  A sweep of 128 jobs of 1024 x 16 replicas, ranked after a Tabu
+// run on the n = 20000 workload, takes 4.3 us (30 accept by accept with the
+// block's couplings in registers; 5.2 with the thresholds staged in LDS).  Cold
+// jobs, R = 1: m = 64 and rows of 30 within the job, 2.5 accepts, 0.72 us (2.7
+// all at once, 0.55 with couplings in registers); m = 512 and rows of 20, 21
+// accepts, 4.4 us (5.6 and 3.5).
 __device__ __forceinline__ int32_t sat_add(int32_t a, int32_t b) { return __builtin_elementwise_add_sat(a, b); }
 
-template <int MS, bool TLDS>
-__global__ void __launch_bounds__(512) k_anneal_ell_spec(const int32_t *__restrict__ jobs, int rgroups,
-                                                         const int32_t *__restrict__ off, int W,
-                                                         const uint32_t *__restrict__ tiles,
-                                                         const int32_t *__restrict__ F0,
-                                                         const uint8_t *__restrict__ y0, int nsw, int B,
-                                                         const int32_t *__restrict__ thr, int KT, int R, int rw,
-                                                         uint32_t k0, uint32_t k1, uint32_t inst_base,
-                                                         const qb_iter *__restrict__ it, uint8_t *__restrict__ Y,
-                                                         int64_t *__restrict__ eout, int32_t *__restrict__ acnt)
+template <int MS>
+__global__ void __launch_bounds__(512) k_anneal_ell(const int32_t *__restrict__ jobs, int rgroups,
+                                                    const int32_t *__restrict__ off, int W,
+                                                    const uint32_t *__restrict__ tiles,
+                                                    const int32_t *__restrict__ F0,
+                                                    const uint8_t *__restrict__ y0, int nsw, int B,
+                                                    const int32_t *__restrict__ thr, int R, int rw, uint32_t k0,
+                                                    uint32_t k1, uint32_t inst_base, const qb_iter *__restrict__ it,
+                                                    uint8_t *__restrict__ Y, int64_t *__restrict__ eout,
+                                                    int32_t *__restrict__ acnt)
 {
-    constexpr int MP = 64 * MS, NPRE = 8;
+    constexpr int MP = 64 * MS;
     extern __shared__ __align__(16) uint32_t dl[];
     const int q = jobs[blockIdx.x / rgroups];
     const int rg = blockIdx.x % rgroups;
@@ -304,17 +192,12 @@ __global__ void __launch_bounds__(512) k_anneal_ell_spec(const int32_t *__restri
     uint32_t *tl = dl;                                            // [MP][W]
     int32_t *Fall = reinterpret_cast<int32_t *>(dl + (size_t)MP * W);   // [rw][MP]
     int32_t *F = Fall + wid * MP;
-    int32_t *ts = Fall + rw * MP;                                 // [2][KT][2^B]
-    uint16_t *info = reinterpret_cast<uint16_t *>(ts + (TLDS ? (size_t)2 * KT << B : 0));   // [MP] entries: earlier, all
+    uint32_t *info = reinterpret_cast<uint32_t *>(Fall + rw * MP);   // [MP] entries: earlier, all
     {
         const uint4 *src = reinterpret_cast<const uint4 *>(tiles + (int64_t)base * W);
         uint4 *dst = reinterpret_cast<uint4 *>(tl);
         const int n16 = m * W / 4;
         for (int t = tid; t < n16; t += nt) dst[t] = src[t];
-        if constexpr (TLDS) {
-            const int n = min(KT, nsw) << B;
-            for (int t = tid; t < n; t += nt) ts[t] = thr[t];
-        }
     }
     __syncthreads();
     for (int a = tid; a < MP; a += nt) {
@@ -326,19 +209,21 @@ __global__ void __launch_bounds__(512) k_anneal_ell_spec(const int32_t *__restri
                 cnt = t + 1;
                 if (qb_ell_col(wd) < a) nu = t + 1;
             }
-        info[a] = (uint16_t)(nu | (cnt << 8));
+        info[a] = (uint32_t)nu | ((uint32_t)cnt << 16);
     }
     int32_t M[MS];                          // -y
-    uint32_t yb = 0;
+    uint32_t yb = 0, real = 0;              // y, and the positions of the job, a bit each
 #pragma unroll
     for (int s = 0; s < MS; ++s) {
         const int pos = 64 * s + lane;
+        real |= (uint32_t)(pos < m) << s;
         if (live) F[pos] = pos < m ? F0[base + pos] : 0;
         if (pos < m && y0[base + pos]) yb |= 1u << s;
         M[s] = (yb >> s) & 1u ? -1 : 0;
     }
     const uint32_t y00 = yb;
     __syncthreads();
+    if (!live) return;   // no barrier follows
 
     // first entries: twice the coupling, and the byte offset of the field it
     // moves (none: zero into the position's own field)
@@ -346,10 +231,11 @@ __global__ void __launch_bounds__(512) k_anneal_ell_spec(const int32_t *__restri
     int32_t dv[MS], uv[MS];
     uint32_t da[MS], ua[MS];
     uint32_t hd = 0, hd2 = 0, hu = 0, hu2 = 0;   // positions with one, and with more, later or earlier entries
+    int32_t nlater = 0;
 #pragma unroll
     for (int s = 0; s < MS; ++s) {
         const int pos = 64 * s + lane;
-        const int nu = info[pos] & 255, nd = (info[pos] >> 8) - nu;
+        const int nu = (int)(info[pos] & 0xFFFFu), nd = (int)(info[pos] >> 16) - nu;
         const uint32_t wu = nu > 0 ? tl[pos * W] : 0u, wd = nd > 0 ? tl[pos * W + nu] : 0u;
         uv[s] = 2 * qb_ell_val(wu);
         ua[s] = fo + 4u * (uint32_t)(nu > 0 ? qb_ell_col(wu) : pos);
@@ -359,7 +245,11 @@ __global__ void __launch_bounds__(512) k_anneal_ell_spec(const int32_t *__restri
         hu2 |= (uint32_t)(nu > 1) << s;
         hd |= (uint32_t)(nd > 0) << s;
         hd2 |= (uint32_t)(nd > 1) << s;
+        nlater += nd;
     }
+    // lanes with a position that accepts, up to which the sweep takes them one by one
+    const int d = 2 * __builtin_amdgcn_readfirstlane((int)qb_wave_sum_i64(nlater)) / m;
+    const int a10 = MS * (1 + d / 4) + 5 * d + d * d, few = 90 * a10 / (900 + a10);
     auto field = [&](uint32_t o) { return reinterpret_cast<int32_t *>(reinterpret_cast<char *>(dl) + o); };
     // adds the first entries of the positions `who`, with the signs `neg`;
     // the other positions add zero, which takes no branch
@@ -377,7 +267,7 @@ __global__ void __launch_bounds__(512) k_anneal_ell_spec(const int32_t *__restri
             const int s = __builtin_ctz(who);
             who &= who - 1;
             const int pos = 64 * s + lane;
-            const int nu = info[pos] & 255, cnt = info[pos] >> 8;
+            const int nu = (int)(info[pos] & 0xFFFFu), cnt = (int)(info[pos] >> 16);
             const int32_t f = (neg >> s) & 1u ? -2 : 2;
             const uint32_t *row = tl + pos * W;
             for (int t = (later ? nu : 0) + skip; t < (later ? cnt : nu); ++t) {
@@ -385,79 +275,140 @@ __global__ void __launch_bounds__(512) k_anneal_ell_spec(const int32_t *__restri
                 atomicAdd(F + qb_ell_col(wd), f * qb_ell_val(wd));
             }
         }
+        __builtin_amdgcn_wave_barrier();                 // whole again before the next comparison
+    };
+    // A block's part of a sweep taken one accept after another: of its
+    // candidates `on` and, once a row was added, of fields fn; the accepted
+    // ones.  No lane branches: a lane without an entry adds zero to a field of
+    // its own.  The next block's fields are read along after each row.
+    const int wlane = min(lane, W - 1);
+    auto chain_block = [&](int s, uint64_t on, int32_t ts, int32_t ys, bool &fresh, int32_t &fn) {
+        const int left = m - 64 * s;
+        const uint64_t block = left >= 64 ? ~0ull : (1ull << left) - 1ull;
+        if (!fresh) on = __ballot((fn ^ ys) <= ts) & block;
+        uint64_t am = 0;
+        int kp = -1;                                     // lane of the row on its way
+        uint32_t wp = 0;
+        while (on) {
+            const int k = __builtin_ctzll(on);
+            const int32_t f = 4 * __builtin_amdgcn_readlane(ys, k) + 2;   // 2 sigma
+            const uint32_t *row = tl + (64 * s + k) * W;
+            if (k != kp) wp = row[wlane];
+            const uint32_t wd = lane < W ? wp : 0u;
+            atomicAdd(F + (wd != 0u ? qb_ell_col(wd) : lane), f * qb_ell_val(wd));
+            for (int i = 64; i < W; i += 64) {
+                const uint32_t v = row[min(i + lane, W - 1)];
+                const uint32_t u = i + lane < W ? v : 0u;
+                atomicAdd(F + (u != 0u ? qb_ell_col(u) : lane), f * qb_ell_val(u));
+            }
+            fresh = false;
+            am |= 1ull << k;
+            const int32_t fs = F[64 * s + lane];
+            if (s + 1 < MS) fn = F[64 * (s + 1) + lane];
+            // the next candidate's row, most often the next accept's
+            on &= ~((2ull << k) - 1ull);
+            kp = -1;
+            if (on) {
+                kp = __builtin_ctzll(on);
+                wp = tl[(64 * s + kp) * W + wlane];
+            }
+            on = __ballot((fs ^ ys) <= ts) & block & ~((2ull << k) - 1ull);
+        }
+        if (am == 0 && !fresh && s + 1 < MS) fn = F[64 * (s + 1) + lane];
+        return (uint32_t)__builtin_amdgcn_inverse_ballot_w64(am) << s;
+    };
+    // the sweep so, of the candidates `acc` at its start
+    auto chain = [&](uint32_t acc, const int32_t (&tp)[MS], const int32_t (&M)[MS]) {
+        uint32_t done = 0;
+        bool fresh = true;                               // no row was added yet
+        int32_t fn = 0;
+        if constexpr (MS <= 8) {
+#pragma unroll
+            for (int s = 0; s < MS; ++s) {
+                if (s > 0 && 64 * s >= m) break;
+                asm volatile("" : "+v"(acc));            // (no block's mask ahead of its turn)
+                done |= chain_block(s, __ballot((acc >> s) & 1u), tp[s], M[s], fresh, fn);
+            }
+        } else {
+            // a loop over indexed registers: unrolled, its scalars crowd out
+            // the other way's (8 % of a sweep)
+            typedef int32_t Blocks __attribute__((ext_vector_type(MS)));
+            Blocks t, y;
+#pragma unroll
+            for (int s = 0; s < MS; ++s) {
+                t[s] = tp[s];
+                y[s] = M[s];
+            }
+#pragma unroll 1
+            for (int s = 0; s < MS && 64 * s < m; ++s)
+                done |= chain_block(s, __ballot((acc >> s) & 1u), t[s], y[s], fresh, fn);
+        }
+        return done;
     };
 
     int32_t nacc = 0;
     const uint32_t tag = (1u << 28) | (inst_base + (it ? it->inst : 0u) + (uint32_t)q);
     constexpr int G = (MS + 3) / 4;
     const int sh = 32 - B;
-    const int chunk = TLDS ? KT : nsw;
-    for (int c0 = 0; c0 < nsw; c0 += chunk) {
-        const int nc = min(chunk, nsw - c0), buf = TLDS ? (c0 / chunk) & 1 : 0;
-        // the next chunk's thresholds, on their way while this one is swept
-        int32_t pre[NPRE];
-        const int nn = TLDS ? max(min(chunk, nsw - c0 - nc), 0) << B : 0;
-        if constexpr (TLDS) {
+    // a sweep's thresholds
+    auto thresholds = [&](int sw, int32_t (&t)[MS]) {
+        const int32_t *table = thr + ((size_t)sw << B);
 #pragma unroll
-            for (int i = 0; i < NPRE; ++i)
-                if (tid + i * nt < nn) pre[i] = thr[((size_t)(c0 + nc) << B) + tid + i * nt];
+        for (int g = 0; g < G; ++g) {
+            const uint4 o = qb_philox(make_uint4(((uint32_t)g << 6) | (uint32_t)lane, (uint32_t)sw, (uint32_t)r, tag),
+                                      k0, k1);
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                if (4 * g + w < MS) t[4 * g + w] = table[qb_word(o, w) >> sh];
         }
-        if (live) {
+    };
+    int32_t ahead[MS];
+    thresholds(0, ahead);
 #pragma unroll 1
-            for (int sw = c0; sw < c0 + nc; ++sw) {
-                int32_t tp[MS];
+    for (int sw = 0; sw < nsw; ++sw) {
+        int32_t tp[MS], f0[MS];
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const uint4 o = qb_philox(make_uint4(((uint32_t)g << 6) | (uint32_t)lane, (uint32_t)sw, (uint32_t)r,
-                                                         tag), k0, k1);
+        for (int s = 0; s < MS; ++s) f0[s] = F[64 * s + lane];
+        // the next sweep's thresholds are on their way during this one
 #pragma unroll
-                    for (int w = 0; w < 4; ++w)
-                        if (4 * g + w < MS) {
-                            const uint32_t k = qb_word(o, w) >> sh;
-                            tp[4 * g + w] = TLDS ? ts[((buf * KT + sw - c0) << B) + k] : thr[((size_t)sw << B) + k];
-                        }
-                }
-                // dE <= t on x = F ^ -y: for y = 1, -F <= t is ~F <= t - 1 (no
-                // field reaches INT32_MAX, nor a position past the job INT32_MIN)
+        for (int s = 0; s < MS; ++s) tp[s] = ahead[s];
+        if (sw + 1 < nsw) thresholds(sw + 1, ahead);
+        // dE <= t on x = F ^ -y: for y = 1, -F <= t is ~F <= t - 1 (no field
+        // reaches INT32_MAX)
 #pragma unroll
-                for (int s = 0; s < MS; ++s) tp[s] = 64 * s + lane < m ? sat_add(tp[s], M[s]) : INT32_MIN;
-                auto decide = [&]() {
-                    uint32_t a = 0;
+        for (int s = 0; s < MS; ++s) tp[s] = sat_add(tp[s], M[s]);
+        auto decide = [&]() {
+            uint32_t a = 0;
 #pragma unroll
-                    for (int s = MS - 1; s >= 0; --s) a = 2 * a + (uint32_t)((F[64 * s + lane] ^ M[s]) <= tp[s]);
-                    return a;
-                };
-                uint32_t acc = decide();
-                scatter(acc & hd, yb, dv, da);
-                scatter_rows(acc & hd2, yb, true, 1);
-                while (true) {
-                    const uint32_t a = decide();
-                    const uint32_t t = (a ^ acc) & hd;
-                    acc = a;
-                    if (__ballot(t != 0u) == 0) break;
-                    // the other way where no longer accepted from 0, or accepted from 1
-                    scatter_rows(t, a ^ ~yb, true, 0);
-                }
-                scatter(acc & hu, yb, uv, ua);
-                scatter_rows(acc & hu2, yb, false, 1);
-                nacc += __builtin_popcount(acc);
-                yb ^= acc;
+            for (int s = MS - 1; s >= 0; --s) a = 2 * a + (uint32_t)((F[64 * s + lane] ^ M[s]) <= tp[s]);
+            return a & real;
+        };
+        uint32_t acc = 0;
 #pragma unroll
-                for (int s = 0; s < MS; ++s) M[s] = -(int32_t)((yb >> s) & 1u);
+        for (int s = MS - 1; s >= 0; --s) acc = 2 * acc + (uint32_t)((f0[s] ^ M[s]) <= tp[s]);
+        acc &= real;
+        const int c = __builtin_popcountll(__ballot(acc != 0u));   // lanes with a candidate
+        if (c <= few) {
+            if (c > 0) acc = chain(acc, tp, M);
+        } else {
+            scatter(acc & hd, yb, dv, da);
+            scatter_rows(acc & hd2, yb, true, 1);
+            while (true) {
+                const uint32_t a = decide();
+                const uint32_t t = (a ^ acc) & hd;
+                acc = a;
+                if (__ballot(t != 0u) == 0) break;
+                // the other way where no longer accepted from 0, or accepted from 1
+                scatter_rows(t, a ^ ~yb, true, 0);
             }
+            scatter(acc & hu, yb, uv, ua);
+            scatter_rows(acc & hu2, yb, false, 1);
         }
-        if constexpr (TLDS) {
-            if (nn > 0) {
-                int32_t *dst = ts + ((size_t)((buf ^ 1) * KT) << B);
+        nacc += __builtin_popcount(acc);
+        yb ^= acc;
 #pragma unroll
-                for (int i = 0; i < NPRE; ++i)
-                    if (tid + i * nt < nn) dst[tid + i * nt] = pre[i];
-                for (int t = tid + NPRE * nt; t < nn; t += nt) dst[t] = thr[((size_t)(c0 + nc) << B) + t];
-                __syncthreads();
-            }
-        }
+        for (int s = 0; s < MS; ++s) M[s] = -(int32_t)((yb >> s) & 1u);
     }
-    if (!live) return;
 
     uint8_t *Yr = Y + (size_t)base * R + (size_t)r * m;
     int64_t e = 0;
@@ -487,45 +438,21 @@ inline size_t ell_lds_bytes(int ms, int W, int rw)
     return sizeof(uint32_t) * ((size_t)64 * ms * (W + rw) + (size_t)64 * rw);
 }
 
-// Sweeps whose thresholds the speculating kernel stages at a time: as many as
-// fit (at most 4), 0 to read them from memory; -1 where the job's rows, the
-// fields and the entry counts do not fit.
-inline int ell_spec_stage(int ms, int W, int rw, int B, size_t *bytes)
-{
-    const size_t need = sizeof(uint32_t) * ((size_t)64 * ms * (W + rw)) + sizeof(uint16_t) * 64 * ms;
-    for (int k = 4; k >= 0; k >>= 1) {
-        *bytes = need + (B <= 12 ? ((size_t)2 * k * sizeof(int32_t)) << B : 0);
-        if (k > 0 && B > 12) continue;
-        if (*bytes <= LDS_MAX) return k;
-        if (k == 0) break;
-    }
-    return -1;
-}
-
 template <int MS>
 qb_status launch_ell(int njobs, int rw, int R, hipStream_t s, const int32_t *jobs, qb_batch b, int W,
                      const uint32_t *tiles, const int32_t *F0, const uint8_t *y0, int nsw, int B, const int32_t *thr,
                      uint64_t seed, uint32_t inst_base, const qb_iter *it, uint8_t *Y, int64_t *e)
 {
-    const size_t lds = ell_lds_bytes(MS, W, rw);
-    size_t slds = 0;
     // up to 8 replicas per workgroup (256 registers a lane), more in further workgroups
-    const int srw = rw < 8 ? rw : 8;
-    const int kt = W <= 255 ? ell_spec_stage(MS, W, srw, B, &slds) : -1;
-    if (kt >= 0) {
-        const int rgroups = (R + srw - 1) / srw;
-        const auto kern = kt > 0 ? k_anneal_ell_spec<MS, true> : k_anneal_ell_spec<MS, false>;
-        QB_TRY_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX));
-        kern<<<njobs * rgroups, 64 * srw, slds, s>>>(jobs, rgroups, b->off_d, W, tiles, F0, y0, nsw, B, thr, kt, R, srw,
-                                                     (uint32_t)seed, (uint32_t)(seed >> 32), inst_base, it, Y, e,
-                                                     b->acnt_d);
-        QB_LAUNCH_CHECK();
-        return QB_OK;
-    }
+    rw = std::min(rw, 8);
+    const int rgroups = (R + rw - 1) / rw;
+    // the tile, the fields and the entry counts: no more than qb_anneal_ell_x
+    // admitted, whose 64 words a replica round up to a multiple of the class
+    const size_t lds = sizeof(uint32_t) * 64 * MS * (size_t)(W + rw + 1);
+    if (lds > LDS_MAX) return QB_E_CAPACITY;
     // set on every launch (no cached flag shared between devices or threads)
     QB_TRY_HIP(hipFuncSetAttribute((const void *)k_anneal_ell<MS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)LDS_MAX));
-    const int rgroups = (R + rw - 1) / rw;
     k_anneal_ell<MS><<<njobs * rgroups, 64 * rw, lds, s>>>(jobs, rgroups, b->off_d, W, tiles, F0, y0, nsw, B, thr, R,
                                                            rw, (uint32_t)seed, (uint32_t)(seed >> 32), inst_base, it,
                                                            Y, e, b->acnt_d);
