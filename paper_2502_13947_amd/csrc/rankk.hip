@@ -5,6 +5,8 @@
 // of one solution and a range of rows; the changed variables of the range are
 // compacted into an LDS list and every thread adds +-Q[j][i] for its four
 // consecutive columns (Q is symmetric, so column j of Q is row j).
+#include <math.h>
+
 #include <algorithm>
 
 #include "qb_internal.h"
@@ -93,8 +95,8 @@ __global__ void __launch_bounds__(256) k_rankk_valu(const QT *__restrict__ Q, in
 // read once per workgroup in whole 128-byte lines; rows of 144 bytes in LDS
 // give the 16-byte operand reads of 16 lanes distinct banks.  K is split over
 // blockIdx.z and the partial sums are added with integer atomics (exact and
-// order independent).  n = 7000, 256 solutions: 74 us with 64 solutions per
-// workgroup and operands straight from memory, 33 us so.
+// order independent).  A call of n = 7000, 256 solutions: 76 us with 64
+// solutions per workgroup and operands straight from memory, 46 us so.
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int RM_K = 128, RM_N = 128, RM_LD = RM_K + 16;
@@ -227,18 +229,14 @@ __global__ void __launch_bounds__(128 * WM) k_rankk_mfma(const int8_t *__restric
 }
 
 template <int WM>
-qb_status rankk_mfma_go(qb_problem P, int z, const int8_t *dX, int32_t *H, int ncu, hipStream_t s)
+qb_status rankk_mfma_go(qb_problem P, int z, const int8_t *dX, int32_t *H, int split, int ncu, hipStream_t s)
 {
     const int n = P->n;
     const int gx = (n + RM_N - 1) / RM_N, gy = (z + 64 * WM - 1) / (64 * WM);
     const int nk = (n + RM_K - 1) / RM_K;
-    // LDS holds one workgroup of WM = 4 on a compute unit, two of the others
-    const int fit = ncu * (WM == 4 ? 1 : 2);
-    int split = fit / (gx * gy);
-    // six splits at most: past that the atomics cost more than the rows save
-    // (n = 2500, 256 solutions: 20, 20 and 32 us with 4, 6 and 12 splits;
-    // n = 12,000, 40 solutions: 40 and 36 us with 4 and 6)
-    split = std::min({std::max(split, 1), nk, 6});
+    // 304 registers a lane (WM = 4: 256) leave room for one workgroup on a
+    // compute unit, of two waves (WM = 1) for two
+    split = std::max(std::min({split, nk, ncu * (WM == 1 ? 2 : 1) / (gx * gy)}), 1);
     const int steps = (nk + split - 1) / split;
     k_rankk_mfma<WM><<<dim3(gx, gy, (nk + steps - 1) / steps), 128 * WM, 0, s>>>(
         dX, n, z, (const int8_t *)P->Qp, P->ldp, H, RM_K * steps);
@@ -285,15 +283,22 @@ qb_status qb_field_ell_launch(qb_problem P, int z, const uint8_t *X, int32_t *H,
 
 qb_status qb_rankk_mfma_launch(qb_problem P, int z, const int8_t *dX, int32_t *H, hipStream_t s)
 {
-    // all solutions in one workgroup, unless six splits of so few workgroups
-    // leave half the card idle
     int ncu = 0;
     QB_TRY_HIP(qb_cu_count(&ncu));
+    // Every split spares a workgroup n / 128 / split steps of 2 us and costs z n
+    // atomic additions, 7 us a million: least at 48 / sqrt(z), whatever n is
+    // (n = 2500, 256 solutions: 17, 16, 19 and 20 us with 2, 3, 4 and 6; n =
+    // 7000, 64: 31, 27, 26 and 26 with 3, 4, 6 and 8; n = 1000, 2048: 17, 22 and
+    // 37 with 1, 2 and 4).
+    const int split = std::max((int)lrint(48.0 / sqrt((double)z)), 1);
+    // As many solutions a workgroup as leave at least five workgroups for
+    // eight compute units (n = 5000, 256 solutions: 31 us with 128, 34 with 256
+    // in a workgroup; n = 7000: 49 and 48; n = 2500: 16 with 64, 17 with 128).
     const int64_t gx = (P->n + RM_N - 1) / RM_N;
     int wm = z <= 64 ? 1 : z <= 128 ? 2 : 4;
-    while (wm > 1 && 12 * gx * ((z + 64 * wm - 1) / (64 * wm)) < ncu) wm >>= 1;
-    return wm == 1 ? rankk_mfma_go<1>(P, z, dX, H, ncu, s)
-           : wm == 2 ? rankk_mfma_go<2>(P, z, dX, H, ncu, s) : rankk_mfma_go<4>(P, z, dX, H, ncu, s);
+    while (wm > 1 && 8 * gx * ((z + 64 * wm - 1) / (64 * wm)) * split < 5 * ncu) wm >>= 1;
+    return wm == 1 ? rankk_mfma_go<1>(P, z, dX, H, split, ncu, s)
+           : wm == 2 ? rankk_mfma_go<2>(P, z, dX, H, split, ncu, s) : rankk_mfma_go<4>(P, z, dX, H, split, ncu, s);
 }
 
 extern "C" qb_status qb_rankk(qb_problem P, int32_t z, const int8_t *dX_d, int32_t *H_d, int32_t variant,

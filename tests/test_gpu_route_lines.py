@@ -122,6 +122,27 @@ def test_small_ranks_are_cheap():
     assert ms[1000] <= 1.2 * ms[1025]
 
 
+# the matrix product's splits over K: (n, more solutions, fewer, how much longer
+# more may take): 1.8 and 3.0 times as long where every workgroup that was
+# thought to fit became a split, 1.3 and 1.7 times with fewer
+@pytest.mark.parametrize("n,more,fewer,line", [(7000, 128, 64, 1.5), (1000, 2048, 512, 2.3)])
+def test_rankk_splits_no_more_than_pays(n, more, fewer, line):
+    P = dense_problem(n, 100, 11)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    ms = {}
+    for z in (more, fewer):
+        dX = torch.randint(-1, 2, (z, n), generator=g, device=DEV, dtype=torch.int8)
+        H = torch.zeros((z, n), dtype=torch.int32, device=DEV)
+
+        def calls():
+            for _ in range(50):
+                qb().rankk(P, dX, H, 2)
+        ms[z] = best_ms(calls) / 50
+    print(f"rankk n {n}: " + "  ".join(f"z {z} {v:.4f}" for z, v in ms.items()) + " ms", flush=True)
+    assert ms[more] <= line * ms[fewer]
+
+
 def ell_jobs(n, z, k, m, W, seed):
     """z solutions of k jobs of m random variables on a circulant graph with W
     entries a row: the outputs of qb_extract_ell and its time."""
