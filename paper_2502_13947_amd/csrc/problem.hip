@@ -492,41 +492,48 @@ extern "C" qb_status qb_init_solutions(int32_t n, int32_t z, uint64_t seed, uint
 
 // ------------------------------------------------------------------ field H = X Q
 // Block: 256 columns i x 8 solutions x a range of rows; X staged through LDS,
-// the 8 solutions' bits of a row in one 8-byte word.  What bounds it: the
-// chain of row loads, so the rows are split over blockIdx.z until the card is
-// full (H is zeroed before and the partial sums are added with integer
-// atomics: exact, any order) and 16 loads are in flight at once (n = 2500, 4
-// solutions: 405 us unsplit with one load in flight, 23 us so).
+// two rows of a solution in one word, so that a dot product adds both.  What
+// bounds it: the chain of row loads for few solutions, so the rows are split
+// over blockIdx.z until the card is full (H is zeroed before and the partial
+// sums are added with integer atomics: exact, any order) and 16 loads are in
+// flight at once; the products for many (calls of n = 2500: 4 solutions 251 us
+// unsplit, 14 with a multiplication a row and solution, 10 so; 1024 solutions
+// of a 16-bit problem 511, 693 and 409 us).
 constexpr int FD_ROWS = 64;
 
 __global__ void __launch_bounds__(256) k_field(const int16_t *__restrict__ Q, int n, int z,
                                                const uint8_t *__restrict__ X, int32_t *__restrict__ H, int rows)
 {
+    typedef short v2s __attribute__((ext_vector_type(2)));
     constexpr int ZT = 8;
-    __shared__ __align__(8) uint8_t xs[FD_ROWS][ZT];
+    __shared__ __align__(16) uint32_t xs[FD_ROWS / 2][ZT];
     const int i = blockIdx.x * 256 + threadIdx.x;
     const int p0 = blockIdx.y * ZT;
     const int jb = blockIdx.z * rows, je = min(jb + rows, n);
     int32_t acc[ZT] = {0};
     for (int j0 = jb; j0 < je; j0 += FD_ROWS) {
         __syncthreads();
-#pragma unroll
-        for (int t = threadIdx.x; t < ZT * FD_ROWS; t += 256) {
-            const int pp = t / FD_ROWS, jj = t % FD_ROWS;
-            xs[jj][pp] = (p0 + pp < z && j0 + jj < je) ? X[(int64_t)(p0 + pp) * n + j0 + jj] : 0;
+        {
+            static_assert(ZT * FD_ROWS / 2 == 256, "a word per thread");
+            const int pp = threadIdx.x / (FD_ROWS / 2), j = j0 + 2 * (threadIdx.x % (FD_ROWS / 2));
+            const uint8_t *x = X + (int64_t)(p0 + pp) * n;
+            const uint32_t lo = p0 + pp < z && j < je ? x[j] : 0u, hi = p0 + pp < z && j + 1 < je ? x[j + 1] : 0u;
+            xs[threadIdx.x % (FD_ROWS / 2)][pp] = lo | (hi << 16);
         }
         __syncthreads();
         if (i < n) {
-            const int jn = min(FD_ROWS, je - j0);
-#pragma unroll 16
-            for (int jj = 0; jj < jn; ++jj) {
-                const int32_t q = Q[(int64_t)(j0 + jj) * n + i];
-                const uint2 x = *reinterpret_cast<const uint2 *>(xs[jj]);
+            const int pairs = (min(FD_ROWS, je - j0) + 1) / 2;
+#pragma unroll 8
+            for (int t = 0; t < pairs; ++t) {
+                // (past the last row its own again, times zero)
+                const int j = j0 + 2 * t;
+                const v2s q = {Q[(int64_t)j * n + i], Q[(int64_t)min(j + 1, n - 1) * n + i]};
+                uint32_t x[ZT];
+                *reinterpret_cast<uint4 *>(x) = *reinterpret_cast<const uint4 *>(xs[t]);
+                *reinterpret_cast<uint4 *>(x + 4) = *reinterpret_cast<const uint4 *>(xs[t] + 4);
 #pragma unroll
-                for (int pp = 0; pp < 4; ++pp) {
-                    acc[pp] += q * (int32_t)((x.x >> (8 * pp)) & 255u);
-                    acc[4 + pp] += q * (int32_t)((x.y >> (8 * pp)) & 255u);
-                }
+                for (int pp = 0; pp < ZT; ++pp)
+                    acc[pp] = __builtin_amdgcn_sdot2(q, __builtin_bit_cast(v2s, x[pp]), acc[pp], false);
             }
         }
     }

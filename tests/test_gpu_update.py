@@ -39,3 +39,24 @@ def test_rankk_field_energy_at_the_edges(n, z, variant):
     E = torch.zeros(z, dtype=torch.int64, device="cuda")
     qb.energy(Xd, F, E)
     assert (E.cpu().numpy() == oracle.energy(X1, Ho)).all()
+
+
+@pytest.mark.parametrize("n,z", [(1, 1), (2, 9), (63, 8), (65, 17), (255, 33), (257, 1), (1023, 3), (1025, 130),
+                                 (2047, 5)])
+def test_field_of_16_bit_problems(n, z):
+    """The least and the largest coefficients, odd numbers of rows, one range
+    of rows and several, parts of a group of eight solutions: exact."""
+    from paper_2502_13947_amd import qb
+    print("field16", n, z, flush=True)
+    rng = np.random.default_rng(7 * n + z)
+    Q = np.triu(rng.choice(np.array([-32768, -32767, -1, 0, 5, 32767], dtype=np.int16), (n, n)))
+    Q = Q + np.triu(Q, 1).T
+    P = qb.Problem(torch.as_tensor(Q, device="cuda"))
+    X = rng.integers(0, 2, (z, n)).astype(np.uint8)
+    X[0] = 1
+    raw = torch.zeros(z * n + 1, dtype=torch.uint8, device="cuda")
+    Xd = raw[1:].view(z, n)
+    Xd.copy_(torch.as_tensor(X, device="cuda"))
+    H = torch.full((z, n), -3, dtype=torch.int32, device="cuda")
+    qb.field(P, Xd, H)
+    assert (H.cpu().numpy() == X.astype(np.int64) @ Q.astype(np.int64)).all()
