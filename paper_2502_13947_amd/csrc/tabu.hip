@@ -145,7 +145,7 @@ template <int TB>
 using TabuFlip = std::conditional_t<(TB > 256), uint16_t, int32_t>;
 
 template <int EPT, typename QT, bool K32, int TB>
-__global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp, const int16_t *__restrict__ Q16,
+__global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp, const int32_t *__restrict__ diag,
                                              int n, uint8_t *__restrict__ X, int32_t *__restrict__ H,
                                              int64_t *__restrict__ E, int alpha, int tenure, int asp,
                                              int32_t *__restrict__ Tout, int32_t *__restrict__ LFout,
@@ -195,7 +195,7 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
         const int j = e * TB + tid;
         if (j < n) {
             const int32_t x = X[ro + j] & 1;
-            const int32_t qjj = Q16[(int64_t)j * n + j];
+            const int32_t qjj = diag[j];
             S[e] = Row::place(e, x ? -S0 : S0);
             xb |= (uint32_t)x << e;
             Kb[e] = (((uint32_t)(qjj + (x ? -2 : 2) * H[ro + j]) + bias) << EB) | (uint32_t)e;
@@ -430,7 +430,7 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
         const int j = e * TB + tid;
         h[e] = 0;
         if (j < n) {
-            const int32_t qjj = Q16[(int64_t)j * n + j];
+            const int32_t qjj = diag[j];
             h[e] = ((int32_t)(((Kb[e] & ~TBIT) >> EB) - bias) - qjj) * (((xb >> e) & 1u) ? -2 : 2) / 4;
             // the diagonal's part of the move to x_min (zero in the Tabu copy)
             if ((pb >> e) & 1u) h[e] += ((xb >> e) & 1u) ? -qjj : qjj;
@@ -496,7 +496,7 @@ qb_status launch_one(const QT *Qt, int ldp, qb_problem P, int z, uint8_t *X, int
     const int lds = 8 * P->n + ring * flip;
     QB_TRY_HIP(hipFuncSetAttribute((const void *)k_tabu<EPT, QT, K32, TB>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    lds));
-    k_tabu<EPT, QT, K32, TB><<<z, TB, lds, s>>>(Qt, ldp, P->Q, P->n, X, H, E, alpha, tenure, asp, T, LF, bias, ring);
+    k_tabu<EPT, QT, K32, TB><<<z, TB, lds, s>>>(Qt, ldp, P->diag, P->n, X, H, E, alpha, tenure, asp, T, LF, bias, ring);
     QB_LAUNCH_CHECK();
     return QB_OK;
 }
