@@ -222,7 +222,8 @@ __device__ __forceinline__ void load_columns_of(const TT *__restrict__ row, int 
             t[0][i] = (uint32_t)*reinterpret_cast<const Pair *>(row + 2 * i * MS + b0) |
                       ((uint32_t)*reinterpret_cast<const Pair *>(row + (2 * i + 1) * MS + b0) << 16);
         }
-        // (a few loads at a time: all at once would spill)
+        // (a few loads at a time: a wave has 168 registers, and MS = 16 of int8
+        // spills 141 words a lane as it is, MS = 8 of int16 20)
         if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
 }

@@ -52,7 +52,7 @@
 // What bounds it: one wave's chain of about 230 instructions and four LDS
 // round trips per step.  Hence no 64-bit address and no branch between the
 // winner and its row (a buffer load by the row's scalar offset), and the rare
-// branches out of the way: 0.774 -> 0.748 us per step (n = 20,000 of degree
+// branches out of the way: 0.70 -> 0.65 us per step (n = 20,000 of degree
 // 4, 16 solutions, tenure 133).
 #include "qb_internal.h"
 
