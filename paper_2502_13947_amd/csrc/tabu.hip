@@ -367,12 +367,13 @@ __global__ void __launch_bounds__(TB) k_tabu(const QT *__restrict__ Qt, int ldp,
         }
         if (__builtin_expect(__ballot(step >= nexp) != 0, 0)) {
             // the elements that are late in any lane, four at a time: their
-            // steps are read together
+            // steps are read together (n = 7000, a step in the mean: 0.68 us,
+            // 0.70 with every element looked at in turn, 0.72 with the lanes'
+            // masks shuffled together)
             nexp = 0x7fffffff;
-            uint32_t any = late;
+            uint32_t any = 0;
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) any |= (uint32_t)__shfl_xor((int)any, o, 64);
-            any = (uint32_t)__builtin_amdgcn_readfirstlane((int)any);
+            for (int e = 0; e < EPT; ++e) any |= __ballot((late >> e) & 1u) ? 1u << e : 0u;
 #pragma unroll 1
             while (any) {
                 int el[4], u[4];
@@ -485,8 +486,8 @@ qb_status launch_one(const QT *Qt, int ldp, qb_problem P, int z, uint8_t *X, int
     // The ring holds the tenure's flips (a power of two of them, 1024 or
     // more) as far as LDS has room: every tenure up to n below 15,600
     // variables, 8191 beyond.  Past it each release is looked up: n = 7000,
-    // tenure 1024, 0.79 us a step with a ring of 2048 and 3.3 with 1024
-    // (n / 150: 0.73); n = 16384, tenure 5000, 0.90 and 2.8.
+    // tenure 1024, 0.76 us a step with a ring of 2048 and 3.6 with 1024
+    // (n / 150: 0.68); n = 16384, tenure 5000, 0.88 and 3.2.
     constexpr int LDS_MAX = 160 * 1024, fixed = 24 * TabuShape<TB>::NW + 4 * (TB + 4) + 64;   // static arrays
     constexpr int flip = (int)sizeof(TabuFlip<TB>);
     const int room = LDS_MAX - fixed - 8 * P->n;
