@@ -235,9 +235,20 @@ qb_status rankk_mfma_go(qb_problem P, int z, const int8_t *dX, int32_t *H, int s
     const int gx = (n + RM_N - 1) / RM_N, gy = (z + 64 * WM - 1) / (64 * WM);
     const int nk = (n + RM_K - 1) / RM_K;
     // 304 registers a lane (WM = 4: 256) leave room for one workgroup on a
-    // compute unit, of two waves (WM = 1) for two
-    split = std::max(std::min({split, nk, ncu * (WM == 1 ? 2 : 1) / (gx * gy)}), 1);
-    const int steps = (nk + split - 1) / split;
+    // compute unit, of two waves (WM = 1) for two.  A split more where a third
+    // of the units have none: solutions that did not change add nothing (n =
+    // 7000, 256 solutions: 34 and 27 us with 3 and 4 splits for none changed,
+    // 36 and 32 for a third, 48 and 49 for all).
+    const int wgs = gx * gy, fit = ncu * (WM == 1 ? 2 : 1);
+    if (3 * wgs * split <= 2 * ncu && wgs * (split + 1) <= ncu) ++split;
+    // the fewest whose workgroups take at most a tenth more steps one after
+    // another than the best number's (n = 12,000, 65 solutions: 65, 60 and 62
+    // us with 2, 5 and 8)
+    auto chain = [&](int k) { return (wgs * k + fit - 1) / fit * ((nk + k - 1) / k); };
+    int least = chain(1), k = 1;
+    for (int t = 2; t <= std::min(split, nk); ++t) least = std::min(least, chain(t));
+    while (10 * chain(k) > 11 * least) ++k;
+    const int steps = (nk + k - 1) / k;
     k_rankk_mfma<WM><<<dim3(gx, gy, (nk + steps - 1) / steps), 128 * WM, 0, s>>>(
         dX, n, z, (const int8_t *)P->Qp, P->ldp, H, RM_K * steps);
     QB_LAUNCH_CHECK();
