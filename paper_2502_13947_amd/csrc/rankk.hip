@@ -241,13 +241,13 @@ qb_status rankk_mfma_go(qb_problem P, int z, const int8_t *dX, int32_t *H, int s
     // 36 and 32 for a third, 48 and 49 for all).
     const int wgs = gx * gy, fit = ncu * (WM == 1 ? 2 : 1);
     if (3 * wgs * split <= 2 * ncu && wgs * (split + 1) <= ncu) ++split;
-    // the fewest whose workgroups take at most a tenth more steps one after
+    // the fewest whose workgroups take less than a tenth more steps one after
     // another than the best number's (n = 12,000, 65 solutions: 65, 60 and 62
     // us with 2, 5 and 8)
     auto chain = [&](int k) { return (wgs * k + fit - 1) / fit * ((nk + k - 1) / k); };
     int least = chain(1), k = 1;
     for (int t = 2; t <= std::min(split, nk); ++t) least = std::min(least, chain(t));
-    while (10 * chain(k) > 11 * least) ++k;
+    while (10 * chain(k) >= 11 * least) ++k;
     const int steps = (nk + k - 1) / k;
     k_rankk_mfma<WM><<<dim3(gx, gy, (nk + steps - 1) / steps), 128 * WM, 0, s>>>(
         dX, n, z, (const int8_t *)P->Qp, P->ldp, H, RM_K * steps);
