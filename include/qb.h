@@ -332,7 +332,9 @@ qb_status qb_set_anneal_wait_limit(int32_t polls);
 qb_status qb_extract_ell(qb_problem P, qb_batch b, const uint8_t *X_d, const int32_t *H_d, uint32_t *tile_d,
                          int32_t *c_d, int32_t *F0_d, uint8_t *y0_d, void *stream);
 /* qb_anneal on ELL tiles (qb_extract_ell, width W): the same sweep, the same
- * random numbers and thresholds, bit-identical results (Y, e).  rw replicas
+ * random numbers and thresholds, bit-identical results (Y, e).  The tile is
+ * one that qb_extract_ell wrote, or one like it: T[a][b] = T[b][a], a row's
+ * columns ascending, none on the diagonal.  rw replicas
  * share a workgroup and its tile copy (1 <= rw <= 16; 0 = automatic); rw only
  * changes the schedule, never the result.  Capacity as qb_anneal, and
  * m_q * W + rw * 64 * ceil(m_q/64) words must fit the 160 KiB of LDS of one

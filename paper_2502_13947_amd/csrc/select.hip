@@ -133,8 +133,9 @@ __global__ void __launch_bounds__(RANK_SMALL / 2) k_rank_small(int n, int npad, 
 // with a bitonic network in LDS; n = 20000, 16 solutions, keys of up to 47 bits: 45 us,
 // against 323 us with that network on chunks.
 // n is rounded up to 1024 V elements, which a pass costs: V steps by at most a
-// factor of two, and 7 and 20 lie just above n = 7000 and 20000.  Above 20 the elements no longer all fit the registers (n = 25000 and
-// 32768, 16 solutions: 141 and 143 us, against 341 and 378 on chunks).
+// factor of two, and 7 and 20 lie just above n = 7000 and 20000.  Above 20 the
+// elements no longer all fit the registers (n = 25000 and 32768, 16 solutions:
+// 141 and 143 us, against 341 and 378 on chunks).
 constexpr int RANK_WAVES = 16, RANK_MAX_V = 32;
 
 template <int V>
