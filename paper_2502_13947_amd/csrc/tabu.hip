@@ -487,7 +487,7 @@ qb_status launch_one(const QT *Qt, int ldp, qb_problem P, int z, uint8_t *X, int
     // more) as far as LDS has room: every tenure up to n below 15,600
     // variables, 8191 beyond.  Past it each release is looked up: n = 7000,
     // tenure 1024, 0.76 us a step with a ring of 2048 and 3.6 with 1024
-    // (n / 150: 0.68); n = 16384, tenure 5000, 0.88 and 3.2.
+    // (n / 150: 0.70); n = 16384, tenure 5000, 0.88 and 3.2.
     constexpr int LDS_MAX = 160 * 1024, fixed = 24 * TabuShape<TB>::NW + 4 * (TB + 4) + 64;   // static arrays
     constexpr int flip = (int)sizeof(TabuFlip<TB>);
     const int room = LDS_MAX - fixed - 8 * P->n;
